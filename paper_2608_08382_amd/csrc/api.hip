@@ -252,7 +252,8 @@ int partition(const llmv_trace* tr, const ChunkMap& cm, int64_t* wg_first,
 typedef void (*TileKernel)(const Params, const NoVars);
 
 TileKernel pick_tiles(int mode, int hist, bool share) {
-  if (mode == MODE_FEAT) return k_tiles<MODE_FEAT, HIST_NONE, false>;
+  if (mode == MODE_FEAT)
+    return share ? k_tiles<MODE_FEAT, HIST_NONE, true> : k_tiles<MODE_FEAT, HIST_NONE, false>;
   if (mode == MODE_SUMS) return k_tiles<MODE_SUMS, HIST_NONE, false>;
   if (hist == HIST_NONE)
     return share ? k_tiles<MODE_ATTR, HIST_NONE, true> : k_tiles<MODE_ATTR, HIST_NONE, false>;
@@ -282,7 +283,8 @@ template <typename VT> struct LongPick;
 template <> struct LongPick<NoVars> {
   typedef void (*K)(const Params, const NoVars, int64_t);
   static K get(int mode, int hist, bool share) {
-    if (mode == MODE_FEAT) return k_long<MODE_FEAT, HIST_NONE, false>;
+    if (mode == MODE_FEAT)
+      return share ? k_long<MODE_FEAT, HIST_NONE, true> : k_long<MODE_FEAT, HIST_NONE, false>;
     if (mode == MODE_SUMS) return k_long<MODE_SUMS, HIST_NONE, false>;
     if (hist == HIST_NONE)
       return share ? k_long<MODE_ATTR, HIST_NONE, true> : k_long<MODE_ATTR, HIST_NONE, false>;
@@ -322,6 +324,7 @@ int run_step(const Params& P, bool want_tenant, hipStream_t stream) {
 
 // Partition + tiles (+ tenant reduction) shared by attribute and features.
 // V: the kernel's second argument (the extended model, or nothing).
+// want_share: per-request outputs, the shares or (MODE_FEAT) the feature rows.
 template <typename VT>
 int run_tiles(int mode, const llmv_trace* tr, Params& P, const VT& V, int32_t T,
               bool want_tenant, bool want_share, void* ws, size_t ws_bytes, hipStream_t stream) {
@@ -893,7 +896,7 @@ int llmv_features(const llmv_trace* trace, const llmv_shape* shape, float* x_req
   P.x_req = x_req;
   P.x_batch = x_batch;
   if (!x_req && !x_batch) return LLMV_OK;
-  return run_tiles(MODE_FEAT, trace, P, NoVars{}, 0, false, false, ws, ws_bytes,
+  return run_tiles(MODE_FEAT, trace, P, NoVars{}, 0, false, x_req != nullptr, ws, ws_bytes,
                    (hipStream_t)stream);
 }
 

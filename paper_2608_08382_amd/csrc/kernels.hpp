@@ -100,10 +100,17 @@ enum { MODE_ATTR = 0, MODE_FEAT = 1, MODE_EXT = 2, MODE_SUMS = 3 };
 // modes that form the batch sums of p*c
 template <int MODE> constexpr bool kCrossSum = MODE == MODE_EXT || MODE == MODE_SUMS;
 template <int MODE> constexpr bool kAttrMode = MODE == MODE_ATTR || MODE == MODE_EXT;
+// Kernel instances with per-request outputs (SHARE: the shares, or under
+// MODE_FEAT the feature rows, are requested).  The staged ones pass them
+// through LDS for coalesced stores.
+template <int MODE, int HIST, bool SHARE>
+constexpr bool kPerRequest = MODE != MODE_SUMS && (SHARE || HIST != 0);
+template <int MODE, bool SHARE> constexpr bool kStaged = MODE != MODE_SUMS && SHARE;
 
 // Native vectors: 16-byte global loads / stores (dwordx4).
 typedef int32_t v4i __attribute__((ext_vector_type(4)));
 typedef float v4f __attribute__((ext_vector_type(4)));
+typedef float v4fu __attribute__((ext_vector_type(4), aligned(4)));  // at any float's address
 enum { HIST_NONE = 0, HIST_LDS = 1, HIST_GLOBAL = 2 };
 
 // Lane slots of a tile kernel instance: the wide tile where it is faster
@@ -390,26 +397,12 @@ __device__ __forceinline__ void cache_flush(double* base, double* out) {
   }
 }
 
-// Per-request epilogue: the share (+ tenant histogram) or the feature row.
-// Shares: k0 + k1*p + k2*c + k3*p^2 (+ k4*p*c under the extended model, k[4])
+// Per-request epilogue: the share (+ tenant histogram).  Shares: k0 + k1*p + k2*c + k3*p^2 (+ k4*p*c under the extended model, k[4])
 // in fp32 from the batch's constants (themselves evaluated in fp64),
 // relative error a few fp32 ulp.
 template <int MODE, int HIST, bool SHARE>
-__device__ __forceinline__ float request_out(const Params& P, const float* k, const double* kd,
-                                             int32_t p, int32_t c, double* s_hist, int32_t t,
-                                             int64_t i) {
-  if (MODE == MODE_FEAT) {
-    if (P.x_req) {
-      const double pd = (double)p;
-      const int64_t N = P.N;
-      P.x_req[0 * N + i] = (float)kd[0];
-      P.x_req[1 * N + i] = (float)(P.S[1] * pd);
-      P.x_req[2 * N + i] = (float)(P.S[2] * (double)c);
-      P.x_req[3 * N + i] = (float)(P.S[3] * (pd * pd));
-      P.x_req[4 * N + i] = (float)kd[1];
-    }
-    return 0.0f;
-  }
+__device__ __forceinline__ float request_out(const Params& P, const float* k,
+                                             int32_t p, int32_t c, double* s_hist, int32_t t) {
   float s = share_of(k, p, c);
   if constexpr (MODE == MODE_EXT) s = fmaf(k[4], (float)p * (float)c, s);
   if (HIST == HIST_LDS) atomicAdd(s_hist + t, (double)s);
@@ -523,9 +516,6 @@ __device__ __forceinline__ int64_t uni(int64_t v) {
 __device__ __forceinline__ float uni_f32(float v) {
   return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, v)));
 }
-__device__ __forceinline__ double uni_f64(double v) {
-  return __builtin_bit_cast(double, (uint64_t)uni((int64_t)__builtin_bit_cast(uint64_t, v)));
-}
 
 // The sum over the 64 lanes (integer, modulo 2^64), wave-uniform.  DPP
 // steps (no LDS): a shuffle would go through the LDS and wait behind the
@@ -573,17 +563,19 @@ __device__ __forceinline__ void load_slots(const Params& P, int64_t x, int32_t* 
   }
 }
 
-// Writes one round of shares staged lane-major in the wave's LDS stage
-// (lane l: slots s0 + kVec*l .. s0 + kVec*l + kVec-1, pitch kStagePitch) so
-// that every global store instruction writes 1 KB of consecutive shares.
-// Only slots in [xf, L) are written.  BATCH: every group's stage read is
+// Writes one round of per-request values (shares, or one feature row) staged
+// lane-major in the wave's LDS stage (lane l: slots s0 + kVec*l .. s0 +
+// kVec*l + kVec-1, pitch kStagePitch) to dst + slot, so that every global
+// store instruction writes 1 KB of consecutive values.  Only slots in
+// [xf, L) are written.  V4: the store's vector type (v4f where dst is 16-byte
+// aligned at every multiple of 4 slots, v4fu where it need not be).  BATCH: every group's stage read is
 // issued before the first store, so that the reads wait once (a wave's LDS
 // operations complete in order, behind the round's tenant-sum atomics)
 // instead of once per store; it holds the round's shares in 28 more
 // registers, which the tile kernel affords and k_long (at its register
 // limit) does not.
-template <int VEC, bool BATCH>
-__device__ __forceinline__ void store_round(const Params& P, float* stage, int64_t ra, int32_t s0,
+template <int VEC, bool BATCH, typename V4 = v4f>
+__device__ __forceinline__ void store_round(float* __restrict__ dst, const float* stage, int32_t s0,
                                             int32_t xf, int32_t L) {
   LLMV_TILE_CONSTANTS(VEC);
   const int lane = threadIdx.x & 63;
@@ -605,14 +597,59 @@ __device__ __forceinline__ void store_round(const Params& P, float* stage, int64
     const int32_t x = s0 + e;              // slot within the tile
     const v4f v = BATCH ? val[BATCH ? g : 0] : *(const v4f*)&stage[(e / kVec) * kStagePitch + (e % kVec)];
     if (x >= xf && x + 4 <= L) {
-      __builtin_nontemporal_store(v, (v4f*)(P.share + ra + x));  // not re-read
+      __builtin_nontemporal_store((V4)v, (V4*)(dst + x));  // not re-read
     } else {
 #pragma unroll
       for (int q = 0; q < 4; ++q)
-        if (x + q >= xf && x + q < L) P.share[ra + x + q] = v[q];
+        if (x + q >= xf && x + q < L) dst[x + q] = v[q];
     }
   }
   wave_lds_sync();
+}
+
+// The feature rows of one round of a tile or long batch (llmv_features):
+// (S0/|B|, S1*p, S2*c, S3*p^2, |B|) of lane l's slots, each row staged in LDS
+// and stored by store_round.  Bound by the 20 bytes written per request: a
+// 62M-request trace takes 0.455 ms (3.9 TB/s); stored straight from the lanes,
+// 4 bytes each and 112 apart, it took 3.90 ms.  Row k starts at x_req + k*N, which is
+// 16-byte aligned only when k*N is a multiple of 4: v4fu stores.
+// base: the request of slot 0; s0: the round's first slot.  consts(q, f):
+// f[0] = S0/|B|, f[1] = |B| of slot q's batch.
+template <int VEC, typename F>
+__device__ __forceinline__ void feature_rows(const Params& P, float* stage, int64_t base,
+                                             int32_t s0, int32_t xf, int32_t L, const int32_t* pv,
+                                             const int32_t* cv, F&& consts) {
+  LLMV_TILE_CONSTANTS(VEC);
+  float* mine = stage + (threadIdx.x & 63) * kStagePitch;
+  float* dst = P.x_req + base;
+  float v[kVec];
+  auto put = [&](int row) {
+#pragma unroll
+    for (int g = 0; g < kVec / 4; ++g)
+      *(v4f*)&mine[4 * g] = (v4f){v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]};
+    store_round<VEC, true, v4fu>(dst + row * P.N, stage, s0, xf, L);
+  };
+#pragma unroll
+  for (int q = 0; q < kVec; ++q) v[q] = (float)(P.S[2] * (double)cv[q]);
+  put(2);
+#pragma unroll
+  for (int q = 0; q < kVec; ++q) v[q] = (float)(P.S[1] * (double)pv[q]);
+  put(1);
+#pragma unroll
+  for (int q = 0; q < kVec; ++q) v[q] = (float)(P.S[3] * ((double)pv[q] * (double)pv[q]));
+  put(3);
+  float n[kVec];
+#pragma unroll
+  for (int q = 0; q < kVec; ++q) {
+    float f[2];
+    consts(q, f);
+    v[q] = f[0];
+    n[q] = f[1];
+  }
+  put(0);
+#pragma unroll
+  for (int q = 0; q < kVec; ++q) v[q] = n[q];
+  put(4);
 }
 
 // Buffer resource over n int32 elements from base (both wave-uniform,
@@ -666,9 +703,9 @@ __device__ __forceinline__ void long_batch(const Params& P, const typename VarsO
                            double* s_hist) {
   constexpr int VEC = kVecOf<MODE, HIST>;
   LLMV_TILE_CONSTANTS(VEC);
-  constexpr bool OUT = MODE != MODE_SUMS;  // per-request outputs
+  constexpr bool OUT = kPerRequest<MODE, HIST, SHARE>;
   constexpr bool TEN = OUT && HIST != HIST_NONE;
-  constexpr bool STAGE = kAttrMode<MODE> && SHARE;
+  constexpr bool STAGE = kStaged<MODE, SHARE>;
   const int lane = threadIdx.x & 63;
   const int64_t ra = uni(rs & ~(int64_t)3);
   const int32_t xf = uni((int32_t)(rs - ra));  // first slot of the batch
@@ -704,7 +741,6 @@ __device__ __forceinline__ void long_batch(const Params& P, const typename VarsO
     }
   };
   // the batch model on lane 0; every lane gets the share constants
-  double kd[4] = {0.0, 0.0, 0.0, 0.0};
   float k[5] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
   auto model = [&]() {
     sp = wave_sum(sp);
@@ -726,17 +762,20 @@ __device__ __forceinline__ void long_batch(const Params& P, const typename VarsO
       // the constants are wave-uniform: held in scalar registers
       wave_lds_sync();
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        kd[q] = uni_f64(wk[q]);
-        k[q] = uni_f32((float)kd[q]);
-      }
+      for (int q = 0; q < 4; ++q) k[q] = uni_f32((float)wk[q]);
       if constexpr (MODE == MODE_EXT) k[4] = uni_f32((float)wk4[0]);
     }
   };
   auto out = [&](const int32_t* pv, const int32_t* cv, const int32_t* tv, int32_t r) {
-    const int32_t s = r * kRoundSlots + x0;
     const uint32_t v = vmask(r);
     const int32_t m = (int32_t)m_of(r);
+    if constexpr (MODE == MODE_FEAT) {
+      feature_rows<VEC>(P, stage, ra, r * kRoundSlots, xf, L, pv, cv, [&](int, float* f) {
+        f[0] = k[0];
+        f[1] = k[1];
+      });
+      return;
+    }
 #pragma unroll
     for (int g = 0; g < kVec / 4; ++g) {
       if (4 * g >= m) break;  // no lane holds a slot of this group (wave-uniform)
@@ -746,11 +785,11 @@ __device__ __forceinline__ void long_batch(const Params& P, const typename VarsO
         const int q = 4 * g + qq;
         sv[qq] = 0.0f;
         if ((v >> q) & 1u)
-          sv[qq] = request_out<MODE, HIST, SHARE>(P, k, kd, pv[q], cv[q], s_hist, tv[q], ra + s + q);
+          sv[qq] = request_out<MODE, HIST, SHARE>(P, k, pv[q], cv[q], s_hist, tv[q]);
       }
       if (STAGE) *(v4f*)&stage[lane * kStagePitch + 4 * g] = (v4f){sv[0], sv[1], sv[2], sv[3]};
     }
-    if (STAGE) store_round<VEC, false>(P, stage, ra, r * kRoundSlots, xf, L);
+    if (STAGE) store_round<VEC, false>(P.share + ra, stage, r * kRoundSlots, xf, L);
   };
 
   int32_t p0[kVec], c0[kVec], t0[kVec];
@@ -878,13 +917,13 @@ __global__ __launch_bounds__(kWG) void k_tiles(const Params P,
   LLMV_TILE_CONSTANTS(VEC);
   extern __shared__ double s_hist[];  // [hist_rep][n_tenants] when HIST_LDS
   __shared__ WaveLds<VEC> s_wave[kWaves];
-  constexpr bool STAGE = kAttrMode<MODE> && SHARE;
+  constexpr bool STAGE = kStaged<MODE, SHARE>;
   constexpr bool EXT = MODE == MODE_EXT;
   constexpr bool RSUM = kCrossSum<MODE>;
   // extended model, per wave: sum p*c and the share constant k4 of each batch
   __shared__ uint64_t s_rsum[RSUM ? kWaves * kTileBatches : 1];
   __shared__ double s_k4[EXT ? kWaves * kTileBatches : 1];
-  __shared__ float s_stage[STAGE ? kWaves * 64 * kStagePitch : 1];  // shares, per wave
+  __shared__ float s_stage[STAGE ? kWaves * 64 * kStagePitch : 1];  // shares or a feature row, per wave
   constexpr bool TEN = HIST != HIST_NONE;
   // the share constants of a lane's first two batches read ahead (see the
   // per-request loop)
@@ -1111,11 +1150,27 @@ __global__ __launch_bounds__(kWG) void k_tiles(const Params P,
           // ---- per request: share (+ tenant) or features
   #pragma unroll
           for (int r = 0; r < kRounds; ++r) {
-            if (MODE == MODE_SUMS || r * kRoundSlots >= L) break;  // wave-uniform
-            const int64_t pos = ra + r * kRoundSlots + x0;
+            if (!kPerRequest<MODE, HIST, SHARE> || r * kRoundSlots >= L) break;  // wave-uniform
+            if constexpr (MODE == MODE_FEAT) {
+              uint32_t kc = 0xffffffffu;
+              float f0 = 0.0f, f1 = 0.0f;
+              feature_rows<VEC>(P, stage, ra, r * kRoundSlots, xf, L, pv[r], cv[r],
+                                [&](int q, float* f) {
+                if ((valid[r] >> q) & 1u) {
+                  const uint32_t k = ord0[r] + __builtin_popcount(bits[r] & ((2u << q) - 1u)) - 1u;
+                  if (k != kc) {
+                    kc = k;
+                    f0 = (float)W.k[k][0];
+                    f1 = (float)W.k[k][1];
+                  }
+                }
+                f[0] = f0;
+                f[1] = f1;
+              });
+              continue;
+            }
             uint32_t kcur = 0xffffffffu;
             float kk[5] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
-            double kd[4] = {0.0, 0.0, 0.0, 0.0};
             // PRE: the share constants of the lane's first two batches are
             // read before its first tenant-sum atomic.  A read between the
             // atomics waits for every atomic before it (LDS operations of a
@@ -1155,19 +1210,20 @@ __global__ __launch_bounds__(kWG) void k_tiles(const Params P,
 #pragma unroll
                       for (int j = 0; j < 5; ++j) kk[j] = kb[j];
                     } else {
-                      kd[0] = W.k[k][0]; kd[1] = W.k[k][1]; kd[2] = W.k[k][2]; kd[3] = W.k[k][3];
-                      kk[0] = (float)kd[0]; kk[1] = (float)kd[1]; kk[2] = (float)kd[2]; kk[3] = (float)kd[3];
+                      kk[0] = (float)W.k[k][0]; kk[1] = (float)W.k[k][1];
+                      kk[2] = (float)W.k[k][2]; kk[3] = (float)W.k[k][3];
                       if constexpr (EXT) kk[4] = (float)W_k4[k];
                     }
                   }
-                  sv[qq] = request_out<MODE, HIST, SHARE>(P, kk, kd, pv[r][q], cv[r][q], s_hist_lane,
-                                                          tv[r][q], pos + q);
+                  sv[qq] = request_out<MODE, HIST, SHARE>(P, kk, pv[r][q], cv[r][q], s_hist_lane,
+                                                          tv[r][q]);
                 }
               }
               if (kAttrMode<MODE> && SHARE)
                 *(v4f*)&stage[lane * kStagePitch + 4 * g] = (v4f){sv[0], sv[1], sv[2], sv[3]};
             }
-            if (kAttrMode<MODE> && SHARE) store_round<VEC, true>(P, stage, ra, r * kRoundSlots, xf, L);
+            if (kAttrMode<MODE> && SHARE)
+              store_round<VEC, true>(P.share + ra, stage, r * kRoundSlots, xf, L);
           }
         }
         wave_lds_sync();
@@ -1391,7 +1447,7 @@ __global__ __launch_bounds__(kWG, 2) void k_long(const Params P, const typename 
                                               int64_t rows) {
   constexpr int VEC = kVecOf<MODE, HIST>;
   LLMV_TILE_CONSTANTS(VEC);
-  constexpr bool STAGE = kAttrMode<MODE> && SHARE;
+  constexpr bool STAGE = kStaged<MODE, SHARE>;
   constexpr bool TEN = HIST != HIST_NONE;
   extern __shared__ double s_hist[];  // HIST_LDS: [hist_rep][n_tenants]; HIST_GLOBAL: the cache
   __shared__ double s_k[kWaves][4];
