@@ -108,9 +108,10 @@ int llmv_shape_constants(const llmv_shape *shape, double S[4]);
 size_t llmv_workspace_size(int64_t n_batches, int64_t n_requests, int32_t n_tenants);
 
 /* Bytes of device workspace llmv_attribute_sweep needs for a trace of this
- * size: llmv_workspace_size's (with a histogram per setting of a pass)
- * plus the (batch, tenant) groups: 20 bytes per request, 40 bytes per batch
- * and a few KiB. */
+ * size: llmv_workspace_size's plus the (batch, tenant) groups: 20 bytes per
+ * request and 40 bytes per batch, and what a round of settings takes: up to
+ * 4 bytes per request and 64 MiB of segment bits and up to 64 bytes per
+ * request and 48 MiB of partial sums (at least 1 KiB per tenant). */
 size_t llmv_sweep_workspace_size(int64_t n_batches, int64_t n_requests, int32_t n_tenants);
 
 /* llmv_sweep_workspace_size for llmv_attribute_sweep_ext: 4 more bytes per
@@ -223,12 +224,12 @@ int llmv_attribute_ext(const llmv_trace *trace, const llmv_shape *shape,
  *   out      device [n_shapes][n_coeffs][n_tenants] fp64, overwritten:
  *            out[(s*n_coeffs + v)*n_tenants + u] = L_u under (s, v).
  * Equivalent to n_shapes*n_coeffs calls of llmv_attribute with only
- * tenant_sums requested, up to rounding: the shares of one tenant's requests
- * in one batch are summed in closed form, k0*n + k1*sum p + k2*sum c +
- * k3*sum p^2 with the batch's fp32 constants and the group's sums rounded to
- * fp32, and added in fp64.  The (batch, tenant) groups are formed once per
- * call; each pass over them evaluates 8 consecutive settings (4 above 1024
- * tenants, 2 above 2048).  n_tenants must be <= 4096 here.  The workspace is
+ * tenant_sums requested, up to rounding: the requests of one tenant in one
+ * batch are merged into a group, whose sums of p, c and p^2 are rounded to
+ * fp32; a setting's sum is its coefficients times the tenant's feature sums
+ * over the groups of each phase and segment, all in fp64.  The groups are
+ * formed once per call; each round over them evaluates up to 1024 consecutive
+ * settings.  n_tenants must be <= 4096 here.  The workspace is
  * llmv_sweep_workspace_size's. */
 int llmv_attribute_sweep(const llmv_trace *trace, const llmv_shape *shapes,
                          int32_t n_shapes, const float *coeffs, int32_t n_coeffs,
@@ -242,10 +243,9 @@ int llmv_attribute_sweep(const llmv_trace *trace, const llmv_shape *shapes,
  *   coeffs   host [n_coeffs][28] finite fp32, laid out as in
  *            llmv_attribute_ext.
  * Equivalent, up to rounding, to n_shapes*n_coeffs calls of
- * llmv_attribute_ext with only tenant_sums requested: a group's shares sum
- * to k0*n + k1*sum p + k2*sum c + k3*sum p^2 + k5*sum p*c, with k0 holding
- * the a6 term and k5 = fp32(a5*S5), the group's sums rounded to fp32.
- * Regimes come from the exact batch sums, as in llmv_attribute_ext.  Other
+ * llmv_attribute_ext with only tenant_sums requested, as
+ * llmv_attribute_sweep is to llmv_attribute (a group also carries its sum of
+ * p*c, rounded to fp32).  Regimes come from the exact batch sums, as in llmv_attribute_ext.  Other
  * arguments, limits (sum p*c per batch below 2^63, not checked) and errors
  * as llmv_attribute_sweep; the workspace is llmv_sweep_workspace_size_ext's. */
 int llmv_attribute_sweep_ext(const llmv_trace *trace, const llmv_shape *shapes,

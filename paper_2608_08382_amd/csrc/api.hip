@@ -90,28 +90,8 @@ int hist_replicas(int32_t T) {
   return 1;
 }
 
-// Settings per what-if pass for T tenants (T <= kHistLdsMax): 8, 4 or 2
-// fp64 histograms of T + hot-tenant replicas, at most 65 KiB of LDS, so that
-// with the kernel's own LDS two workgroups fit in a CU's 160 KiB.
-constexpr size_t kSweepHistLds = 65 * 1024;
-int sweep_group(int32_t T) {
-  for (int g = kSweepG; g > 1; g /= 2)
-    if ((size_t)g * (size_t)(T + kHotSlots) * sizeof(double) <= kSweepHistLds) return g;
-  return 1;
-}
-static_assert(2 * (kHistLdsMax + kHotSlots) * sizeof(double) <= kSweepHistLds, "sweep LDS");
-
-template <int NC>
-using SweepKernel = void (*)(const GroupSweep, const VarTableOf<NC>);
-template <int NC>
-SweepKernel<NC> pick_sweep(int g) {
-  if (g >= 8) return k_sweep_groups<8, NC>;
-  if (g >= 4) return k_sweep_groups<4, NC>;
-  return k_sweep_groups<2, NC>;
-}
-
 struct Layout {
-  size_t wg_first, claims, partials, counts, hot, flag, big_list, big_seg, long_list, total;
+  size_t wg_first, claims, partials, flag, big_list, big_seg, long_list, total;
 };
 
 // Chunks for `workers` wave workers over n requests, for wave tiles of `cap`
@@ -154,9 +134,8 @@ ChunkMap chunk_map(int64_t n, int64_t workers, bool pieces, int64_t cap,
   return m;
 }
 
-// Workspace layout shared by every entry point for n requests; rows =
-// histograms per workgroup (settings per pass in the what-if sweep, else 1).
-Layout layout(int64_t n, int32_t T, int rows = 1) {
+// Workspace layout shared by every entry point for n requests.
+Layout layout(int64_t n, int32_t T) {
   Layout L{};
   size_t o = 0;
   const int64_t grid = grid_max_for(n);
@@ -165,12 +144,8 @@ Layout layout(int64_t n, int32_t T, int rows = 1) {
                 sizeof(int64_t));
   L.claims = o;  // the launch's counters
   o += align_up(kCounters * sizeof(unsigned long long));
-  L.partials = o;  // [grid][rows][T]
-  if (lds_hist(T)) o += align_up((size_t)grid * (size_t)rows * (size_t)T * sizeof(double));
-  L.counts = o;  // what-if sweep: requests per tenant, and the hot tenants
-  if (lds_hist(T)) o += align_up((size_t)T * sizeof(unsigned long long));
-  L.hot = o;
-  o += align_up(kHot * sizeof(int32_t));
+  L.partials = o;  // [grid][T]
+  if (lds_hist(T)) o += align_up((size_t)grid * (size_t)T * sizeof(double));
   L.flag = o;
   o += align_up(sizeof(int));
   // batches of more than kListMin requests, listed with their segments
@@ -185,40 +160,74 @@ Layout layout(int64_t n, int32_t T, int rows = 1) {
   return L;
 }
 
-// The what-if sweep's groups after a Layout ending at o: slice table, slice
-// group counts and offsets, batch group offsets, exact batch sums, scan tile
-// sums, and the groups (at most one per request, plus a tile of slack that
-// the sweep tiles read past the last group); under the extended model a
-// fourth batch sum and the groups' sums of p*c.
+// The what-if sweep's arrays after a Layout ending at o: slice table, exact
+// batch sums, segment masks, the groups' offsets and the groups (at most one
+// per request; under the extended model with their sums of p*c and a fifth
+// batch sum), the settings and the runs' contributions.
 struct GroupLayout {
-  size_t first, scnt, soff, gofs, bsum, tsum, gw, gf, gr, part2, total;
+  size_t first, bsum, mask, mask_words, cells, tot, base, groups, shapes, raw, table, diff, part, total;
+  int W;       // workgroups of the group build
+  int chunks;  // chunks of the sum kernel, at most
+  int blocks;  // 64-setting blocks per round, at most (1, 2, 4, 8 or 16)
 };
-// part2: a second set of pass partials ([grid][rows][T], as the Layout's),
-// which a pass writes while the next pass folds the other.
-GroupLayout group_layout(size_t o, int64_t nB, int64_t N, bool ext, int32_t T = 0, int rows = 1) {
+// Workgroups of the group build: each with at least a request per tenant
+// (its row of cells has 2 words per tenant) and 64 per wave, at most three
+// per compute unit.
+int build_grid(int64_t N, int32_t T) {
+  const int64_t per = T > 64 * kWaves ? T : 64 * kWaves;
+  const int64_t w = (N + per - 1) / per;
+  return (int)(w < 1 ? 1 : (w > 768 ? 768 : w));
+}
+// Requests per slice for that many workgroups: as many slices for every wave
+// (a wave with one more than another would be waited for), each of about
+// kSlice requests or, in a shorter trace, one slice per wave.
+int64_t slice_size(int64_t N, int W) {
+  const int64_t waves = (int64_t)W * kWaves;
+  const int64_t turns = (N + waves * kSlice - 1) / (waves * kSlice);
+  const int64_t s = ((N + waves * turns - 1) / (waves * turns) + 63) / 64 * 64;
+  return s < kMinSlice ? kMinSlice : s;
+}
+GroupLayout group_layout(size_t o, int64_t nB, int64_t N, bool ext, int32_t T) {
   GroupLayout G{};
-  const int64_t nS = (N + kSlice - 1) / kSlice;
-  const int64_t nt = (nS + kScanTile - 1) / kScanTile;
+  const int32_t t = lds_hist(T) ? T : 0;
+  G.W = build_grid(N, t);
   G.first = o;
-  o += align_up((size_t)(nS + 1) * sizeof(int64_t));
-  G.scnt = o;
-  o += align_up((size_t)(nS + 1) * sizeof(int64_t));
-  G.soff = o;
-  o += align_up((size_t)(nS + 1) * sizeof(int64_t));
-  G.gofs = o;
-  o += align_up((size_t)(nB + 1) * sizeof(int64_t));
+  // the launch may take fewer workgroups than G.W: at most this many slices
+  o += align_up((size_t)(N / (kSlice / 2) + 768 * kWaves + 2) * sizeof(int64_t));
   G.bsum = o;
-  o += align_up((size_t)((ext ? 5 : 4) * nB + 1) * sizeof(unsigned long long));
-  G.tsum = o;
-  o += align_up((size_t)(nt + 1) * sizeof(int64_t));
-  G.gw = o;
-  o += align_up((size_t)(N + kGT) * sizeof(uint32_t));
-  G.gf = o;
-  o += align_up((size_t)(N + kGT) * sizeof(v4f));
-  G.gr = o;
-  if (ext) o += align_up((size_t)(N + kGT) * sizeof(float));
-  G.part2 = o;
-  if (lds_hist(T)) o += align_up((size_t)grid_max_for(N) * (size_t)rows * (size_t)T * sizeof(double));
+  o += align_up((size_t)((ext ? 5 : 4) * nB) * sizeof(int64_t));
+  // a segment bit per batch and setting: 64 settings per batch, and room for
+  // more settings per round, up to 64 MiB
+  const size_t more = (size_t)(N < (int64_t)1 << 24 ? N : (int64_t)1 << 24) * 4;
+  G.mask = o;
+  G.mask_words = (size_t)nB + more / sizeof(uint64_t);
+  o += align_up(G.mask_words * sizeof(uint64_t));
+  G.cells = o;
+  o += align_up((size_t)G.W * 2 * (size_t)t * sizeof(uint32_t));
+  G.tot = o;
+  o += align_up(2 * (size_t)t * sizeof(uint32_t));
+  G.base = o;
+  o += align_up((2 * (size_t)t + 1) * sizeof(int64_t));
+  G.groups = o;
+  o += align_up((size_t)N * (ext ? sizeof(Group<true>) : sizeof(Group<false>)));
+  G.shapes = o;
+  o += align_up(sizeof(ShapeArgs));
+  G.raw = o;
+  o += align_up((size_t)kSweepRound * 28 * sizeof(float));
+  G.table = o;
+  o += align_up((size_t)kSweepRows<7> * kSweepRound * sizeof(double));
+  G.diff = o;
+  o += align_up(2 * 64 * 8 * sizeof(double));
+  const int64_t ch = (N + kSumMinChunk - 1) / kSumMinChunk;
+  G.chunks = (int)(ch < kWaves ? kWaves : (ch > kSumChunks ? kSumChunks : ch / kWaves * kWaves));
+  // rounds as long as their contributions fit 48 MiB, in a short trace 64
+  // bytes per request
+  const size_t rows = (size_t)(G.chunks + 2 * t);
+  const size_t most = N < (int64_t)786432 ? (size_t)N * 64 : (size_t)48 << 20;
+  G.blocks = kSweepRound / 64;
+  while (G.blocks > 1 && rows * G.blocks * 64 * sizeof(double) > most) G.blocks /= 2;
+  G.part = o;
+  o += align_up(rows * G.blocks * 64 * sizeof(double));
   G.total = o;
   return G;
 }
@@ -491,6 +500,19 @@ int admit_run(const int64_t* sums, const uint8_t* phase, int64_t n_batches,
   return LLMV_OK;
 }
 
+constexpr int kFewMost = 32;  // settings of a round summed by k_sweep_few
+
+// The sum kernel for rounds of `blocks` 64-setting blocks: the fewest blocks
+// per wave that hold the round in at most two waves side by side.
+typedef void (*SumKernel)(const SweepSum);
+template <int NC>
+SumKernel pick_sum(int blocks, int* nblk) {
+  if (blocks <= 1) return *nblk = 1, k_sweep_sum<NC, 1>;
+  if (blocks <= 2) return *nblk = 2, k_sweep_sum<NC, 2>;
+  if (blocks <= 4) return *nblk = 4, k_sweep_sum<NC, 4>;
+  return *nblk = 8, k_sweep_sum<NC, 8>;
+}
+
 // The what-if sweep under Eq. 1 (NC = 5) or the extended model (NC = 7).
 template <int NC>
 int sweep_run(const llmv_trace* trace, const llmv_shape* shapes, int32_t n_shapes,
@@ -507,161 +529,187 @@ int sweep_run(const llmv_trace* trace, const llmv_shape* shapes, int32_t n_shape
   if (!out) return fail(LLMV_EINVAL, "out is NULL");
   for (int64_t i = 0; i < (int64_t)n_coeffs * 4 * NC; ++i)
     if (!std::isfinite(coeffs[i])) return fail(LLMV_EINVAL, "coeffs[%lld] is not finite", (long long)i);
-  double S[64][6];  // S0..S3 (and S5, S6)
-  if (n_shapes > 64) return fail(LLMV_EINVAL, "n_shapes=%d > 64", n_shapes);
+  ShapeArgs A{};
+  if (n_shapes > kSweepShapes) return fail(LLMV_EINVAL, "n_shapes=%d > %d", n_shapes, kSweepShapes);
   for (int s = 0; s < n_shapes; ++s) {
     const llmv_shape* sh = shapes ? &shapes[s] : nullptr;
-    rc = EXT ? shape_constants_ext(sh, S[s]) : shape_constants(sh, S[s]);
+    rc = EXT ? shape_constants_ext(sh, A.S[s]) : shape_constants(sh, A.S[s]);
     if (rc) return rc;
   }
   int cus = 0;
   rc = device_cus(&cus);
   if (rc) return rc;
   const int64_t nB = trace->n_batches, N = trace->n_requests;
-  // One pass over the groups per G consecutive settings (shape-major, as in
-  // out); each pass keeps G tenant histograms in LDS.
-  const int G = sweep_group(n_tenants);
-  const Layout L = layout(N, n_tenants, G);
-  const GroupLayout GL = group_layout(L.total, nB, N, EXT, n_tenants, G);
-  rc = check_ws(ws, ws_bytes, GL.total);
+  const int32_t T = n_tenants;
+  const Layout L = layout(N, T);
+  const GroupLayout G = group_layout(L.total, nB, N, EXT, T);
+  rc = check_ws(ws, ws_bytes, G.total);
   if (rc) return rc;
   char* base = (char*)ws;
   const int64_t n_var = (int64_t)n_shapes * n_coeffs;
   if (N == 0) {  // no requests: every tenant sum is zero
-    const int64_t n_out = n_var * n_tenants;
+    const int64_t n_out = n_var * T;
     int64_t blocks = (n_out + kWG - 1) / kWG;
     if (blocks > 1024) blocks = 1024;
     hipLaunchKernelGGL(k_zero_f64, dim3((unsigned)blocks), dim3(kWG), 0, st, out, n_out);
     HIP_TRY(hipGetLastError(), "k_zero_f64 launch");
     return LLMV_OK;
   }
-  const size_t dyn = (size_t)G * (size_t)(n_tenants + kHotSlots) * sizeof(double);
-  const SweepKernel<NC> kern = pick_sweep<NC>(G);
-  const int64_t grid = grid_for(N, cus, blocks_per_cu(kern, dyn, kSweepWG));
-  unsigned long long* claims = (unsigned long long*)(base + L.claims);
 
-  // the most frequent tenants get replicated histogram entries
-  unsigned long long* counts = (unsigned long long*)(base + L.counts);
-  int32_t* hot = (int32_t*)(base + L.hot);
-  hipLaunchKernelGGL(k_zero_u64, dim3(16), dim3(kWG), 0, st, counts, (int64_t)n_tenants);
-  HIP_TRY(hipGetLastError(), "k_zero_u64 launch");
-  int64_t blocks = (N + (int64_t)kWG * 64 - 1) / ((int64_t)kWG * 64);
-  blocks = blocks < 1 ? 1 : (blocks > 2048 ? 2048 : blocks);
-  hipLaunchKernelGGL(k_tenant_count, dim3((unsigned)blocks), dim3(kWG),
-                     (size_t)n_tenants * sizeof(unsigned int), st, trace->tenant, N, n_tenants,
-                     counts);
-  HIP_TRY(hipGetLastError(), "k_tenant_count launch");
-  hipLaunchKernelGGL(k_hot_tenants, dim3(1), dim3(kWG), 0, st, (const unsigned long long*)counts,
-                     n_tenants, hot);
-  HIP_TRY(hipGetLastError(), "k_hot_tenants launch");
+  // the exact batch sums, with the phase in the first row
+  int64_t* bsum = (int64_t*)(base + G.bsum);
+  {
+    Params P{};
+    rc = shape_constants(nullptr, P.S);
+    if (rc) return rc;
+    P.off = trace->offsets;
+    P.p = trace->p;
+    P.c = trace->c;
+    P.nB = nB;
+    P.N = N;
+    P.bsums = bsum;
+    P.phase_bit = kPrefillBit;
+    const hipEvent_t before = g_ev_before;  // the hook is for llmv_attribute and llmv_features
+    g_ev_before = nullptr;
+    const hipEvent_t after = g_ev_after;
+    g_ev_after = nullptr;
+    rc = run_tiles(EXT ? MODE_SUMS : MODE_FEAT, trace, P, NoVars{}, 0, false, false, ws, ws_bytes, st);
+    g_ev_before = before;
+    g_ev_after = after;
+    if (rc) return rc;
+  }
 
-  // the groups: counts and exact batch sums per slice, slice offsets, then
-  // the groups themselves
-  const int64_t nS = (N + kSlice - 1) / kSlice;
-  int64_t* first = (int64_t*)(base + GL.first);
-  int64_t* scnt = (int64_t*)(base + GL.scnt);
-  int64_t* soff = (int64_t*)(base + GL.soff);
-  int64_t* gofs = (int64_t*)(base + GL.gofs);
-  unsigned long long* bsum = (unsigned long long*)(base + GL.bsum);
-  int64_t* tsum = (int64_t*)(base + GL.tsum);
-  uint32_t* gw = (uint32_t*)(base + GL.gw);
-  v4f* gf = (v4f*)(base + GL.gf);
-  float* gr = EXT ? (float*)(base + GL.gr) : nullptr;
+  // the groups: counts per workgroup and bin, their offsets, the groups
+  const int64_t resident = (int64_t)cus * blocks_per_cu(k_group_emit<EXT>, 2 * (size_t)T * sizeof(uint32_t));
+  const int W = (int)(resident < G.W ? resident : G.W);
+  const int64_t slice = slice_size(N, W);
+  const int64_t nS = (N + slice - 1) / slice;
+  const int bins = 2 * T;
+  int64_t* first = (int64_t*)(base + G.first);
+  uint32_t* cells = (uint32_t*)(base + G.cells);
+  uint32_t* tot = (uint32_t*)(base + G.tot);
+  int64_t* gbase = (int64_t*)(base + G.base);
+  Group<EXT>* groups = (Group<EXT>*)(base + G.groups);
   ChunkMap sm{};  // equal slices, none claimed
-  sm.s1 = kSlice;
+  sm.s1 = slice;
   sm.s2 = 1;
   sm.n_static = nS;
   sm.n_chunks = nS;
-  sm.F = nS * kSlice;
-  rc = partition(trace, sm, first, claims, st);
+  sm.F = nS * slice;
+  rc = partition(trace, sm, first, (unsigned long long*)(base + L.claims), st);
   if (rc) return rc;
-  hipLaunchKernelGGL(k_zero_u64, dim3(256), dim3(kWG), 0, st, bsum, (EXT ? 5 : 4) * nB);
-  HIP_TRY(hipGetLastError(), "k_zero_u64 launch");
-  int64_t bgrid = (nS + kWaves - 1) / kWaves;
-  const int64_t bcap = (int64_t)cus * blocks_per_cu(k_group_build<true, EXT>, 0);
-  if (bgrid > bcap) bgrid = bcap;
-  hipLaunchKernelGGL((k_group_build<false, EXT>), dim3((unsigned)bgrid), dim3(kWG), 0, st,
-                     trace->offsets, trace->p, trace->c, trace->tenant, nB, N, (const int64_t*)first,
-                     nS, scnt, bsum, (const int64_t*)nullptr, (int64_t*)nullptr, (uint32_t*)nullptr,
-                     (v4f*)nullptr, (float*)nullptr);
-  HIP_TRY(hipGetLastError(), "k_group_build launch");
-  const int64_t nt = (nS + kScanTile - 1) / kScanTile;  // >= 1
-  hipLaunchKernelGGL(k_scan_tiles, dim3((unsigned)nt), dim3(kScanWG), 0, st, (const int64_t*)scnt, nS,
-                     tsum);
-  HIP_TRY(hipGetLastError(), "k_scan_tiles launch");
-  hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(kScanWG), 0, st, tsum, nt);
-  HIP_TRY(hipGetLastError(), "k_scan_top launch");
-  hipLaunchKernelGGL(k_scan_apply, dim3((unsigned)nt), dim3(kScanWG), 0, st, (const int64_t*)scnt, nS,
-                     (const int64_t*)tsum, soff);
-  HIP_TRY(hipGetLastError(), "k_scan_apply launch");
-  hipLaunchKernelGGL((k_group_build<true, EXT>), dim3((unsigned)bgrid), dim3(kWG), 0, st,
-                     trace->offsets, trace->p, trace->c, trace->tenant, nB, N, (const int64_t*)first,
-                     nS, (int64_t*)nullptr, (unsigned long long*)nullptr, (const int64_t*)soff, gofs,
-                     gw, gf, gr);
-  HIP_TRY(hipGetLastError(), "k_group_build launch");
+  hipLaunchKernelGGL(k_group_count, dim3(W), dim3(kWG), (2 + kWaves) * (size_t)T * sizeof(uint32_t),
+                     st, trace->offsets, (const int64_t*)bsum, trace->tenant, nB, N,
+                     (const int64_t*)first, nS, slice, T, cells);
+  HIP_TRY(hipGetLastError(), "k_group_count launch");
+  hipLaunchKernelGGL(k_group_cols, dim3((bins + 63) / 64), dim3(64 * kColWaves), 0, st, cells, W,
+                     bins, tot);
+  HIP_TRY(hipGetLastError(), "k_group_cols launch");
+  hipLaunchKernelGGL(k_group_base, dim3(1), dim3(kScanWG), 0, st, (const uint32_t*)tot, bins,
+                     gbase);
+  HIP_TRY(hipGetLastError(), "k_group_base launch");
+  hipLaunchKernelGGL(k_group_emit<EXT>, dim3(W), dim3(kWG), 2 * (size_t)T * sizeof(uint32_t),
+                     st, trace->offsets, (const int64_t*)bsum, trace->p, trace->c, trace->tenant, nB,
+                     N, (const int64_t*)first, nS, slice, T, (const uint32_t*)cells,
+                     (const int64_t*)gbase, groups);
+  HIP_TRY(hipGetLastError(), "k_group_emit launch");
 
-  // the passes: the chunks of k_tiles over the batches; every launch takes
-  // exactly n_chunks claims (one per chunk it runs, the static ones
-  // included), so launch i starts at claim i * n_chunks
-  const ChunkMap cm = chunk_map(N, grid * kSweepWaves, false, kCapNarrow);  // one static chunk per wave
-  int64_t* wg_first = (int64_t*)(base + L.wg_first);
-  rc = partition(trace, cm, wg_first, claims, st);
-  if (rc) return rc;
-  GroupSweep Q{};
-  Q.off = trace->offsets;
-  Q.gofs = gofs;
-  Q.bsum = bsum;
-  Q.gw = gw;
-  Q.gf = gf;
-  Q.gr = gr;
-  Q.nB = nB;
-  Q.wg_first = wg_first;
-  Q.claims = claims;
-  Q.n_chunks = cm.n_chunks;
-  Q.partials = (double*)(base + L.partials);
-  Q.n_tenants = n_tenants;
-  Q.hot = hot;
-  // pass i writes partials bufs[i % 2] and folds pass i - 1's from the
-  // other buffer (when its sums fit the fold's mapping); the last pass's, or
-  // every pass's otherwise, go to k_tenant_reduce
-  double* bufs[2] = {(double*)(base + L.partials), (double*)(base + GL.part2)};
-  const bool fold = grid <= (int64_t)kFoldGroups * kFoldRows &&
-                    (int64_t)G * n_tenants <= (int64_t)kFoldPer * grid;
-  int64_t launch = 0;
-  int64_t pv0 = 0;  // the previous pass's first setting
-  int32_t pn = 0;   // and its settings
-  for (int64_t v0 = 0; v0 < n_var; v0 += G, ++launch) {
-    VarTableOf<NC> V{};
-    V.n = (int32_t)(n_var - v0 < G ? n_var - v0 : G);
-    for (int g = 0; g < V.n; ++g) {
-      const int64_t v = v0 + g;
-      const int s = (int)(v / n_coeffs);
-      const int64_t j = v % n_coeffs;
-      for (int k = 0; k < NC - 1; ++k) V.S[g][k] = S[s][k];
-      for (int i = 0; i < 4 * NC; ++i) V.th[g][i] = (double)coeffs[j * 4 * NC + i];
-      for (int r = 0; r < 4; ++r) {
-        for (int k = 1; k < 4; ++k) V.K[g][r][k - 1] = (float)(V.th[g][r * NC + k] * S[s][k]);
-        if (EXT) V.K[g][r][3] = (float)(V.th[g][r * NC + 5] * S[s][4]);
-      }
+  // rounds of at most kSweepRound settings (consecutive in out), as many as
+  // the masks have room for; with more coefficient vectors than a round
+  // holds, a round stays within one shape
+  Settings V{};
+  V.raw = (const float*)(base + G.raw);
+  V.S = (const double*)(base + G.shapes);
+  V.n_coeffs = n_coeffs;
+  V.table = (double*)(base + G.table);
+  V.diff = (double*)(base + G.diff);
+  hipLaunchKernelGGL(k_put_shapes, dim3(1), dim3(64), 0, st, A, n_shapes, (double*)(base + G.shapes));
+  HIP_TRY(hipGetLastError(), "k_put_shapes launch");
+  auto put_coeffs = [&](int64_t j0, int64_t n) {
+    const float* src = coeffs + j0 * 4 * NC;
+    for (int64_t i = 0; i < n * 4 * NC; i += kPutWords) {
+      CoeffArgs C;
+      const int m = (int)(n * 4 * NC - i < kPutWords ? n * 4 * NC - i : kPutWords);
+      memcpy(C.c, src + i, m * sizeof(float));
+      hipLaunchKernelGGL(k_put_coeffs, dim3(1), dim3(256), 0, st, C, m, (float*)(base + G.raw) + i);
+      HIP_TRY(hipGetLastError(), "k_put_coeffs launch");
     }
-    Q.claim_base = (uint64_t)launch * (uint64_t)cm.n_chunks;
-    Q.partials = fold ? bufs[launch & 1] : bufs[0];
-    Q.prev = fold && launch > 0 ? bufs[(launch - 1) & 1] : nullptr;
-    Q.prev_out = out + pv0 * n_tenants;
-    Q.prev_n = pn;
-    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(kSweepWG), dyn, st, Q, V);
-    HIP_TRY(hipGetLastError(), "k_sweep_groups launch");
-    const bool last = v0 + G >= n_var;
-    if (!fold || last) {
-      const int n_hist = V.n * n_tenants;
-      hipLaunchKernelGGL(k_tenant_reduce,
-                         dim3((unsigned)((n_hist + kTenantChunk - 1) / kTenantChunk)),
-                         dim3(64 * kReduceWaves), 0, st, (const double*)Q.partials, (int)grid,
-                         n_hist, out + v0 * n_tenants);
-      HIP_TRY(hipGetLastError(), "k_tenant_reduce launch");
+    return (int)LLMV_OK;
+  };
+  const bool all_held = n_coeffs <= kSweepRound;
+  if (all_held) {
+    rc = put_coeffs(0, n_coeffs);
+    if (rc) return rc;
+  }
+  int64_t room = G.blocks;  // 64-setting blocks per round
+  while (room > 1 && room * nB > (int64_t)G.mask_words) room /= 2;
+  for (int64_t v0 = 0; v0 < n_var;) {
+    int64_t n = n_var - v0 < room * 64 ? n_var - v0 : room * 64;
+    V.jbase = 0;
+    if (!all_held) {
+      const int64_t j0 = v0 % n_coeffs;
+      if (n > n_coeffs - j0) n = n_coeffs - j0;
+      V.jbase = j0;
+      rc = put_coeffs(j0, n);
+      if (rc) return rc;
     }
-    pv0 = v0;
-    pn = V.n;
+    const int blocks = (int)((n + 63) / 64);
+    int nblk = 1;
+    const SumKernel kern = pick_sum<NC>(blocks, &nblk);
+    const int WS = (blocks + nblk - 1) / nblk;  // 1 or 2
+    V.v0 = v0;
+    V.n = (int32_t)n;
+    V.ld = WS * nblk * 64;
+    uint64_t* mask = (uint64_t*)(base + G.mask);
+    // batches per wave: 64 to 512, enough waves to fill the card first
+    int per = 64;
+    while (per < 512 && nB / (2 * per) * blocks >= 16 * (int64_t)cus) per *= 2;
+    const int64_t mx = (nB + (int64_t)per * kWaves - 1) / ((int64_t)per * kWaves);
+    if (mx > 0x7fffffff) return fail(LLMV_EINVAL, "n_batches=%lld too large", (long long)nB);
+    hipLaunchKernelGGL(k_sweep_mask<NC>, dim3((unsigned)mx, blocks), dim3(kWG), 0, st,
+                       (const int64_t*)bsum, nB, V, per, nblk, mask);
+    HIP_TRY(hipGetLastError(), "k_sweep_mask launch");
+    SweepSum Q{};
+    Q.base = gbase;
+    Q.groups = groups;
+    Q.nrow = bsum;
+    Q.mask = mask;
+    Q.table = V.table;
+    Q.diff = V.diff;
+    Q.part = (double*)(base + G.part);
+    Q.nB = nB;
+    Q.bins = bins;
+    Q.ld = V.ld;
+    Q.WS = WS;
+    // Up to 32 settings: the kernel whose lanes take groups, one wave per chunk
+    // (5.4M groups under 4 settings 57 us, against 218 us in the other one,
+    // whose 64 lanes would hold 4); more: the one whose lanes take settings,
+    // one workgroup per chunk (its time is that of 64 settings).
+    int64_t big, chunks;
+    if (n <= kFewMost) {
+      const SumKernel few = n <= 8 ? k_sweep_few<NC, 8> : (n <= 16 ? k_sweep_few<NC, 16> : k_sweep_few<NC, 32>);
+      chunks = kWaves * (int64_t)cus * blocks_per_cu(few, 0);
+      if (chunks > G.chunks) chunks = G.chunks;
+      chunks = (chunks + kWaves - 1) / kWaves * kWaves;
+      big = chunks;
+      hipLaunchKernelGGL(few, dim3((unsigned)(chunks / kWaves)), dim3(kWG), 0, st, Q);
+      HIP_TRY(hipGetLastError(), "k_sweep_few launch");
+    } else {
+      big = (int64_t)cus * blocks_per_cu(kern, 0);
+      if (big > G.chunks) big = G.chunks;
+      chunks = 4 * big < G.chunks ? 4 * big : G.chunks;
+      Q.big = (int32_t)big;
+      hipLaunchKernelGGL(kern, dim3((unsigned)chunks), dim3(kWG), 0, st, Q);
+      HIP_TRY(hipGetLastError(), "k_sweep_sum launch");
+    }
+    // more waves to add long columns of rows where the blocks do not fill the
+    // card by themselves
+    const int out_wg = (T + kOutTenants - 1) / kOutTenants * blocks <= 2 * cus ? 1024 : 256;
+    hipLaunchKernelGGL(k_sweep_out, dim3((T + kOutTenants - 1) / kOutTenants, blocks), dim3(out_wg),
+                       (size_t)out_wg * kOutTenants * sizeof(double), st, (const int64_t*)gbase, T,
+                       (int)chunks, (int)big, (const double*)Q.part, V.ld, (int32_t)n, out + v0 * T);
+    HIP_TRY(hipGetLastError(), "k_sweep_out launch");
+    v0 += n;
   }
   return LLMV_OK;
 }
@@ -736,9 +784,7 @@ static size_t sweep_ws(int64_t n_batches, int64_t n_requests, int32_t n_tenants,
   const int64_t nB = n_batches > 0 ? n_batches : 0;
   const int64_t n = n_requests > 0 ? n_requests : 0;
   const int32_t T = n_tenants > 0 ? n_tenants : 0;
-  const int rows = lds_hist(T) ? sweep_group(T) : 1;
-  const Layout L = layout(n, T, rows);
-  return group_layout(L.total, nB, n, ext, T, rows).total;
+  return group_layout(layout(n, T).total, nB, n, ext, T).total;
 }
 
 size_t llmv_sweep_workspace_size(int64_t n_batches, int64_t n_requests, int32_t n_tenants) {

@@ -2,654 +2,961 @@
 // trace under many (shape, coefficient) settings (Sec. 1, what-if planning;
 // Eq. 1 and Sec. 2 "Problem formulation" for each setting).
 //
-// Within a batch every request's share is k0 + k1*p + k2*c + k3*p^2 with the
-// batch's constants (Eq. 1 under the chosen segment, beta split equally, the
-// a4 term per request), so the shares of one tenant's requests in one batch
-// sum to k0*n + k1*P + k2*C + k3*Q over that group's count n and sums P, C,
-// Q.  The sweep forms these (batch, tenant) groups once per call and then,
-// per setting, adds one term per group instead of one per request.  Under
-// the extended model (NC = 7: the a5 term on p*c, the a6 term per request)
-// a share gains k5*p*c and k0 gains a6*S6, so a group also carries R = its
-// sum of p*c and adds k5*R.
+// Under setting s a request's share is theta . x with theta the coefficient
+// set of its batch's phase and of the segment s chooses for the batch, and x
+// = (S0/|B|, S1*p, S2*c, S3*p^2, |B|) (the extended model, NC = 7, adds
+// S5*p*c and S6).  Only the segment depends on both the setting and the
+// batch, so a tenant's sum is
+//   L_u(s) = sum over phases of  thetaM . (A - C(s)) + thetaC . C(s),
+// A = the tenant's feature sums over all its requests of that phase, C(s) =
+// those over its requests in batches that s makes compute-bound; thetaM and
+// thetaC are the phase's memory- and compute-bound sets times the shape
+// constants.  Requests of one tenant in one batch share the segment and are
+// merged into a group (n, P, C, Q[, R] = count, sum p, sum c, sum p^2[, sum
+// p*c]).  The groups are sorted by (tenant, phase) once per call; then a wave
+// holds 64*NBLK settings, one per lane and block, and walks a tenant's groups,
+// adding each group's features (wave-uniform) in the lanes whose bit of the
+// batch's segment mask is set.  No scattered adds: every sum is in registers.
 //
-//  * k_group_build<false>: per slice of kSlice requests, the number of
-//    groups, and the exact batch sums; k_scan_*: the slices' group offsets;
-//    k_group_build<true>: the groups and each batch's first group.  One wave
-//    per slice; a wave-private LDS hash table keyed by tenant collects the
-//    group sums and is emitted when it fills or the batch part ends (a tenant
-//    emitted twice in one batch only costs an extra group: sums are linear).
-//  * k_sweep_groups<NV, NC>: one pass of NV settings over the groups.  Wave
-//    tiles are runs of whole batches (at most kGB batches, kGT group slots);
-//    lane j evaluates batch j of the tile under every setting into a per-wave
-//    LDS table of (k0, k1, k2, k3) (and k5); lane-local runs of kGV groups then add
-//    their group sums into per-setting fp64 LDS tenant histograms, flushed to
-//    [grid][NV][n_tenants] partials that k_tenant_reduce folds.
+//  * k_group_count: walks slices of the requests, counts each workgroup's
+//    groups per bin (2*tenant + phase); k_group_cols, k_group_base: bin and
+//    workgroup offsets; k_group_emit: the groups, each at its place.
+//  * k_put_shapes, k_put_coeffs: the settings, from kernel arguments.
+//  * k_sweep_mask: the segment bit of every (batch, setting), from the exact
+//    batch sums in fp64 as in MODE_ATTR / MODE_EXT.
+//  * k_sweep_sum: the sums C(s) and the contribution of every run of groups;
+//    k_sweep_out: a tenant's contributions added up.
+// A call of 1024 settings over 100k batches, 12.8M requests and 1024 tenants
+// (5.4M groups) takes 1.50 ms, 1.16 of them in k_sweep_sum; it took 7.06 ms
+// with a pass per 8 settings that added one fp64 LDS atomic per group and
+// setting (64% of the CU cycles LDS-bound).
 #pragma once
+
+#include <type_traits>
 
 #include "kernels.hpp"
 
 namespace llmv {
-
-// ------------------------------------------------------------ settings
-
-// The settings of one pass: shape constants and coefficients
-// (theta[phase][segment][k], NC terms per set, as in Params or ExtModel) of
-// each, and the batch-independent share constants k1..k3 = fp32(theta_a1*S1,
-// theta_a2*S2, theta_a3*S3) and k5 = fp32(theta_a5*S5) of each regime
-// (2*phase + segment), rounded from the same fp64 products as in MODE_ATTR
-// and MODE_EXT.
-constexpr int kSweepG = 8;
-template <int NC>
-struct VarTableOf {
-  static_assert(NC == 5 || NC == 7, "Eq. 1 or the extended model");
-  int32_t n;                    // settings in this pass, 1..kSweepG
-  double S[kSweepG][NC - 1];    // S0..S3 (and S5, S6)
-  double th[kSweepG][4 * NC];
-  float K[kSweepG][4][4];       // [setting][regime][k1, k2, k3, k5 (NC = 7)]
-};
-using VarTable = VarTableOf<5>;
-// Under tenant skew many lanes of one LDS atomic hit the same histogram
-// entry and serialize.  Each of the kHot most frequent tenants gets kHotRep
-// histogram entries per setting (lane l adds into entry l % kHotRep), folded
-// at the end.
-constexpr int kHot = 4;
-constexpr int kHotRep = 4;
-constexpr int kHotSlots = kHot * kHotRep;
-
-// One batch under every setting: k0 of setting g (fp32, rounded from fp64
-// as in MODE_ATTR / MODE_EXT) into k0[g]; returns the segments (bit g).
-// Rsum (sum p*c) is read only under the extended model.
-template <int NV, int NC>
-__device__ __forceinline__ uint32_t sweep_batch(const VarTableOf<NC>& V, int64_t n, uint64_t Psum,
-                                                uint64_t Csum, uint64_t Qsum, uint64_t Rsum,
-                                                bool prefill, float* k0) {
-  (void)Rsum;
-  const int phase = prefill ? 0 : 1;
-  uint32_t segs = 0;
-  for (int g = 0; g < NV; ++g) {
-    const double* S = V.S[g];
-    const double* thm = V.th[g] + (phase * 2 + 0) * NC;
-    const double* thc = V.th[g] + (phase * 2 + 1) * NC;
-    bool comp;
-    if constexpr (NC == 5) {
-      const double X[5] = {S[0], S[1] * (double)Psum, S[2] * (double)Csum, S[3] * (double)Qsum,
-                           (double)n * (double)n};
-      // Roofline max of the two segments; ties stay memory-bound.
-      comp = eq1(thc, X) > eq1(thm, X);
-    } else {
-      const double X[7] = {S[0], S[1] * (double)Psum, S[2] * (double)Csum, S[3] * (double)Qsum,
-                           (double)n * (double)n, S[4] * (double)Rsum, S[5] * (double)n};
-      comp = eq7(thc, X) > eq7(thm, X);
-    }
-    const double* th = comp ? thc : thm;
-    segs |= (uint32_t)comp << g;
-    if constexpr (NC == 5)
-      k0[g] = (float)(th[0] * (S[0] / (double)n) + th[4] * (double)n);
-    else
-      k0[g] = (float)(th[0] * (S[0] / (double)n) + th[4] * (double)n + th[6] * S[5]);
-  }
-  return segs;
-}
-
-// ------------------------------------------------------ hot tenants
-
-// counts[u] += number of requests of tenant u (counts cleared beforehand);
-// a per-workgroup LDS histogram, then one global atomic per tenant.
-__global__ __launch_bounds__(kWG) void k_tenant_count(const int32_t* __restrict__ tenant,
-                                                      int64_t n, int32_t T,
-                                                      unsigned long long* __restrict__ counts) {
-  extern __shared__ unsigned int s_cnt[];
-  for (int u = threadIdx.x; u < T; u += kWG) s_cnt[u] = 0u;
-  __syncthreads();
-  const int64_t stride = (int64_t)gridDim.x * kWG;
-  for (int64_t i = (int64_t)blockIdx.x * kWG + threadIdx.x; i < n; i += stride)
-    atomicAdd(&s_cnt[tenant[i]], 1u);
-  __syncthreads();
-  for (int u = threadIdx.x; u < T; u += kWG)
-    if (s_cnt[u]) atomicAdd(&counts[u], (unsigned long long)s_cnt[u]);
-}
-
-// hot[0..kHot) = the most frequent tenants in decreasing count (ties: the
-// smaller id first); -1 where fewer tenants have requests.  One workgroup.
-__global__ __launch_bounds__(kWG) void k_hot_tenants(const unsigned long long* __restrict__ counts,
-                                                     int32_t T, int32_t* __restrict__ hot) {
-  __shared__ unsigned long long s_best[kWG / 64];
-  __shared__ int32_t s_hot[kHot];
-  const int tid = threadIdx.x, lane = tid & 63;
-  for (int h = 0; h < kHot; ++h) {
-    // key: count (saturated to 32 bits) above the complement of the id
-    unsigned long long best = 0;
-    for (int u = tid; u < T; u += kWG) {
-      bool taken = false;
-      for (int j = 0; j < h; ++j) taken |= (s_hot[j] == u);
-      const unsigned long long c = counts[u] < 0xffffffffull ? counts[u] : 0xffffffffull;
-      const unsigned long long key = (c << 32) | (unsigned long long)(0xffffffffu - (uint32_t)u);
-      if (!taken && c > 0 && key > best) best = key;
-    }
-    for (int m = 32; m >= 1; m >>= 1) {
-      const unsigned long long o = __shfl_xor(best, m, 64);
-      best = o > best ? o : best;
-    }
-    if (lane == 0) s_best[tid >> 6] = best;
-    __syncthreads();
-    if (tid == 0) {
-      unsigned long long b = 0;
-      for (int w = 0; w < kWG / 64; ++w) b = s_best[w] > b ? s_best[w] : b;
-      s_hot[h] = b ? (int32_t)(0xffffffffu - (uint32_t)(b & 0xffffffffull)) : -1;
-    }
-    __syncthreads();
-  }
-  if (tid < kHot) hot[tid] = s_hot[tid];
-}
 
 // ------------------------------------------------------------ group build
 
 constexpr int kGrpSlots = 256;             // hash slots per wave
 constexpr int kGrpFlush = kGrpSlots / 2;   // emit once more slots than this are taken
 constexpr uint32_t kGrpEmpty = 0xffffffffu;
-constexpr int kGrpTenantBits = 12;         // tenant ids of a sweep are below 4096
-constexpr uint32_t kGrpTenantMask = (1u << kGrpTenantBits) - 1u;
-constexpr uint32_t kGrpBatchMask = (1u << (32 - kGrpTenantBits)) - 1u;
-constexpr int64_t kSlice = 2048;           // requests per build slice
-static_assert(kHistLdsMax <= (1 << kGrpTenantBits), "sweep tenant ids fit the group word");
+constexpr int64_t kSlice = 2048;           // requests per build slice, about, in long traces
+constexpr int64_t kMinSlice = 64;          // and at least
+constexpr int kWin = 256;                  // requests per wave and array staged in LDS
 static_assert(kGrpFlush + 64 < kGrpSlots, "a round always finds a free slot");
+static_assert(kWin == 4 * 64, "a window is one 16-byte load per lane and array");
 
-template <bool EXT>
-struct GroupTable {  // one wave's
-  uint32_t key[kGrpSlots];
-  uint32_t n[kGrpSlots];
-  unsigned long long p[kGrpSlots], c[kGrpSlots], q[kGrpSlots];
-  unsigned long long r[EXT ? kGrpSlots : 1];  // sum p*c (EXT)
-};
+// The batch state of a sweep is llmv_batch_sums' rows with the phase in the
+// first one: |B| (at most 2^22) plus kPrefillBit for a prefill batch.
+constexpr int64_t kPrefillBit = (int64_t)1 << 40;
+constexpr int64_t kSizeMask = kPrefillBit - 1;
 
 __device__ __forceinline__ uint32_t grp_hash(uint32_t t) {
   static_assert(kGrpSlots == 256, "8-bit hash");
   return (t * 2654435761u) >> 24;  // Fibonacci hashing
 }
 
-// The requests are cut into slices of kSlice; wave w builds slices w, w + W,
-// ...  A slice emits the groups of every batch part inside it in request
-// order, so all groups are in request order and a batch's groups are
-// contiguous even when slices split it.  first[k] = the first batch starting
-// at or after request k*kSlice (k_partition over equal chunks).
-// WRITE = false: slice_cnt[k] = groups of slice k; bsum[j*nB + b] (zeroed
-// beforehand) += (sum p, sum c, sum p^2, count of c == 0, and with EXT
-// sum p*c) of the part of batch b in the slice.  WRITE = true: the groups
-// from slice_off[k] on, gw = ((b mod 2^20) << 12) | tenant, gf = (n, P, C, Q)
-// and with EXT gr = R (sum p*c), rounded to fp32, and gofs[b] for every
-// batch starting in the slice (gofs[nB] by the last).  Both passes emit the
-// same groups: the emission points depend only on the data.
-template <bool WRITE, bool EXT>
-__global__ __launch_bounds__(kWG) void k_group_build(
-    const int64_t* __restrict__ off, const int32_t* __restrict__ p, const int32_t* __restrict__ c,
-    const int32_t* __restrict__ tenant, int64_t nB, int64_t N, const int64_t* __restrict__ first,
-    int64_t nS, int64_t* __restrict__ slice_cnt, unsigned long long* __restrict__ bsum,
-    const int64_t* __restrict__ slice_off, int64_t* __restrict__ gofs, uint32_t* __restrict__ gw,
-    v4f* __restrict__ gf, float* __restrict__ gr) {
-  __shared__ GroupTable<EXT> s_tab[kWaves];
+// Slices of workgroup w of W: [w*nS/W, (w+1)*nS/W), dealt to its waves in
+// turn.
+__device__ __forceinline__ int64_t slice_lo(int64_t nS, int w, int W) { return nS * w / W; }
+
+// Walks the requests of one slice in rounds of at most 64 consecutive
+// requests of one batch, staged through an LDS window of kWin requests per
+// array: the next window's loads are in flight while the current one is
+// worked on, and 64 batch offsets are read at a time.  first = the first
+// batch starting at or after the slice's first request r0.  For each round:
+// round(j0, cnt, bin_phase, b) with the window index of its first request, its
+// requests, the batch's phase and the batch; returns the groups it opened.  After a
+// round that ends the batch's part in the slice, or once more than kGrpFlush
+// groups are open, emit().  The rounds depend only on the data, so two walks
+// of one slice open and emit the same groups.
+template <int NA, typename Round, typename Emit>
+__device__ __forceinline__ void walk_slice(const int64_t* __restrict__ off,
+                                           const int64_t* __restrict__ nrow, int64_t nB, int64_t r0,
+                                           int64_t r1, int64_t first, const int32_t* const (&src)[NA],
+                                           int32_t (*win)[kWin], Round&& round, Emit&& emit) {
   const int lane = threadIdx.x & 63;
-  GroupTable<EXT>& H = s_tab[threadIdx.x >> 6];
+  const int64_t n = r1 - r0;
+  v4i pre[NA];
+  auto fetch = [&](int64_t at) {  // the window from request r0 + at
+#pragma unroll
+    for (int a = 0; a < NA; ++a)  // past the slice: 0, no memory access
+      pre[a] = load4(elem_rsrc(src[a] + r0, n), (int32_t)at + 4 * lane);
+  };
+  fetch(0);
+  // the batch holding request r0: the last one starting at or before it
+  int64_t b0 = first;  // first batch of the offsets window
+  if (b0 > 0 && (b0 == nB || uni(off[b0]) > r0)) --b0;
+  int64_t ends = 0, nr = 0;  // lane j: batch b0 + j's end and size row
+  auto batches = [&]() {
+    const int64_t b = b0 + lane;
+    ends = b < nB ? off[b + 1] : INT64_MAX;
+    nr = b < nB ? nrow[b] : 0;
+  };
+  batches();
+  int32_t open = 0;
+  int64_t pos = r0, bend = r0, b = b0;
+  int phase = 0;
+  for (int64_t w0 = 0; w0 < n; w0 += kWin) {
+    wave_lds_sync();
+#pragma unroll
+    for (int a = 0; a < NA; ++a) *(v4i*)&win[a][4 * lane] = pre[a];
+    if (w0 + kWin < n) fetch(w0 + kWin);
+    wave_lds_sync();
+    const int64_t wend = min(r1, r0 + w0 + kWin);
+    while (pos < wend) {
+      if (pos == bend) {  // the next nonempty batch
+        uint64_t later = __ballot(ends > pos);
+        while (later == 0) {
+          b0 += 64;
+          batches();
+          later = __ballot(ends > pos);
+        }
+        const int j = __builtin_ctzll(later);
+        b = b0 + j;
+        bend = readlane_i64(ends, j);
+        phase = (readlane_i64(nr, j) & kPrefillBit) ? 0 : 1;
+      }
+      const int64_t part = min(bend, r1);
+      const int32_t cnt = uni((int32_t)(min(min(part, wend), pos + 64) - pos));
+      open += round((int32_t)(pos - r0 - w0), cnt, phase, b);
+      pos += cnt;
+      if (open > kGrpFlush || pos == part) {
+        emit(phase, b, open);
+        open = 0;
+      }
+    }
+  }
+}
+
+// cells[w][2*t + phase] = groups of tenant t in batches of that phase that
+// workgroup w's slices emit.  A wave marks the tenants of its open groups in
+// an LDS table with the number of the current emission; a request whose
+// tenant carries another number opens a group.  (A bin's groups fit 32 bits:
+// 2^32 groups of one tenant and phase are 2^32 nonempty batches, whose trace
+// and workspace exceed the card's memory.)  Dynamic LDS: (2*T + kWaves*T)
+// words.  Bound by the waves' LDS round trips; 4 bytes read per request.
+__global__ __launch_bounds__(kWG) void k_group_count(
+    const int64_t* __restrict__ off, const int64_t* __restrict__ nrow,
+    const int32_t* __restrict__ tenant, int64_t nB, int64_t N, const int64_t* __restrict__ first,
+    int64_t nS, int64_t slice, int32_t T, uint32_t* __restrict__ cells) {
+  extern __shared__ uint32_t s_dyn[];
+  __shared__ __align__(16) int32_t s_win[kWaves][1][kWin];
+  uint32_t* s_cnt = s_dyn;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  uint32_t* tag = s_dyn + 2 * T + wave * T;
+  for (int u = tid; u < 2 * T; u += kWG) s_cnt[u] = 0u;
+  for (int u = lane; u < T; u += 64) tag[u] = 0u;
+  __syncthreads();
+  uint32_t id = 1;
+  const int64_t k1 = slice_lo(nS, blockIdx.x + 1, gridDim.x);
+  for (int64_t k = slice_lo(nS, blockIdx.x, gridDim.x) + wave; k < k1; k += kWaves) {
+    const int64_t r0 = k * slice;
+    const int32_t* const src[1] = {tenant};
+    walk_slice<1>(off, nrow, nB, r0, min(N, r0 + slice), uni(first[k]), src, s_win[wave],
+                  [&](int32_t j0, int32_t cnt, int phase, int64_t) {
+      bool fresh = false;
+      if (lane < cnt) {
+        const int32_t t = s_win[wave][0][j0 + lane];
+        fresh = atomicExch(&tag[t], id) != id;
+        if (fresh) atomicAdd(&s_cnt[2 * t + phase], 1u);
+      }
+      return (int32_t)__builtin_popcountll(__ballot(fresh));
+    }, [&](int, int64_t, int32_t) { ++id; });
+  }
+  __syncthreads();
+  for (int u = tid; u < 2 * T; u += kWG) cells[(int64_t)blockIdx.x * 2 * T + u] = s_cnt[u];
+}
+
+// Per bin: cells becomes the exclusive prefix over the workgroups, tot[bin]
+// the bin's total.  A block of 16 waves takes 64 bins (one per lane); wave v
+// owns rows [v*W/16, (v+1)*W/16).
+constexpr int kColWaves = 16;
+__global__ __launch_bounds__(64 * kColWaves) void k_group_cols(uint32_t* __restrict__ cells, int W,
+                                                              int bins, uint32_t* __restrict__ tot) {
+  __shared__ uint32_t s_sum[kColWaves][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int bin = blockIdx.x * 64 + lane;
+  const int lo = W * wave / kColWaves, hi = W * (wave + 1) / kColWaves;
+  uint32_t s = 0;
+  if (bin < bins) {
+#pragma unroll 8
+    for (int w = lo; w < hi; ++w) s += cells[(int64_t)w * bins + bin];
+  }
+  s_sum[wave][lane] = s;
+  __syncthreads();
+  uint32_t at = 0, all = 0;
+  for (int v = 0; v < kColWaves; ++v) {
+    if (v == wave) at = all;
+    all += s_sum[v][lane];
+  }
+  if (bin >= bins) return;
+  if (wave == 0) tot[bin] = all;
+#pragma unroll 8
+  for (int w = lo; w < hi; ++w) {
+    const uint32_t c = cells[(int64_t)w * bins + bin];
+    cells[(int64_t)w * bins + bin] = at;
+    at += c;
+  }
+}
+
+constexpr int kScanWG = 1024;
+constexpr int kScanPer = 8;  // bins per thread
+static_assert(2 * kHistLdsMax <= kScanWG * kScanPer, "one workgroup scans every bin");
+
+// base[i] = groups in bins below i (i <= bins).  One workgroup.
+__global__ __launch_bounds__(kScanWG) void k_group_base(const uint32_t* __restrict__ tot, int bins,
+                                                        int64_t* __restrict__ base) {
+  __shared__ int64_t s_w[kScanWG / 64];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, i0 = threadIdx.x * kScanPer;
+  int64_t v[kScanPer], s = 0;
+#pragma unroll
+  for (int k = 0; k < kScanPer; ++k) {
+    v[k] = i0 + k < bins ? (int64_t)tot[i0 + k] : 0;
+    s += v[k];
+  }
+  const int64_t x = (int64_t)wave_incl_scan((uint64_t)s);
+  if (lane == 63) s_w[w] = x;
+  __syncthreads();
+  int64_t e = x - s;
+  for (int k = 0; k < w; ++k) e += s_w[k];
+#pragma unroll
+  for (int k = 0; k < kScanPer; ++k) {
+    if (i0 + k <= bins) base[i0 + k] = e;
+    e += v[k];
+  }
+  if (i0 + kScanPer == bins) base[bins] = e;
+}
+
+template <bool EXT>
+struct GroupTable {  // one wave's open groups
+  uint32_t key[kGrpSlots];
+  uint32_t n[kGrpSlots];
+  unsigned long long p[kGrpSlots], c[kGrpSlots], q[kGrpSlots];
+  unsigned long long r[EXT ? kGrpSlots : 1];  // sum p*c (EXT)
+  uint8_t slot[kGrpSlots];                    // slots of the open groups, in order of opening
+};
+
+// A group as k_group_emit writes it: the batch index b (its low 32 bits; the
+// bits above beside n), n, and P, C, Q (with EXT R) rounded to fp32.  One
+// record, so that a group is one scattered write (two arrays of 4 and 16
+// bytes took 218 instead of 189 us for 5.4M groups).
+constexpr int kNBits = 23;  // n <= 2^22
+template <bool EXT>
+struct Group {
+  uint32_t b, nb;
+  float s[EXT ? 4 : 3];
+};
+static_assert(sizeof(Group<false>) == 20 && sizeof(Group<true>) == 24, "records without padding");
+
+// The groups that k_group_count counted, at their places: bin 2*tenant +
+// phase starts at base[bin], workgroup w's part of it at base[bin] +
+// cells[w][bin].  The order of a workgroup's groups within a bin is that of
+// its waves' emissions.  Dynamic LDS: 2*T words.
+// 12.8M requests take 0.19 ms: 0.14 in the LDS chains of the hash table, the
+// rest in the scattered writes (a line each).
+template <bool EXT>
+__global__ __launch_bounds__(kWG) void k_group_emit(
+    const int64_t* __restrict__ off, const int64_t* __restrict__ nrow,
+    const int32_t* __restrict__ p, const int32_t* __restrict__ c,
+    const int32_t* __restrict__ tenant, int64_t nB, int64_t N, const int64_t* __restrict__ first,
+    int64_t nS, int64_t slice, int32_t T, const uint32_t* __restrict__ cells,
+    const int64_t* __restrict__ base, Group<EXT>* __restrict__ out) {
+  extern __shared__ uint32_t s_cur[];  // [2T] next place within the bin
+  __shared__ GroupTable<EXT> s_tab[kWaves];
+  __shared__ __align__(16) int32_t s_win[kWaves][3][kWin];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  GroupTable<EXT>& H = s_tab[wave];
   for (int s = lane; s < kGrpSlots; s += 64) {
     H.key[s] = kGrpEmpty;
     H.n[s] = 0;
-    H.p[s] = 0;
-    H.c[s] = 0;
-    H.q[s] = 0;
+    H.p[s] = H.c[s] = H.q[s] = 0;
     if (EXT) H.r[s] = 0;
   }
-  wave_lds_sync();
-  const int64_t waves = (int64_t)gridDim.x * kWaves;
-  for (int64_t k = (int64_t)blockIdx.x * kWaves + (threadIdx.x >> 6); k < nS; k += waves) {
-    const int64_t r0 = k * kSlice, r1 = min(N, r0 + kSlice);
-    const bool last = k == nS - 1;
-    int64_t b = uni(first[k]);
-    if (b > 0 && (b == nB || uni(off[b]) > r0)) --b;  // the batch holding request r0
-    int64_t out = WRITE ? uni(slice_off[k]) : 0;      // index of the next group
-    for (; b < nB; ++b) {
-      const int64_t bo0 = uni(off[b]), bo1 = uni(off[b + 1]);
-      if (bo0 >= r1 && !last) break;  // the last slice also takes the empty batches at N
-      if (WRITE && bo0 >= r0 && lane == 0) gofs[b] = out;
-      const int64_t lo = max(bo0, r0), hi = min(bo1, r1);
-      int32_t taken = 0;
-      uint64_t sp = 0, sc = 0, sq = 0, sz = 0, sr = 0;
-      for (int64_t base = lo; base < hi; base += 64) {
-        const int64_t i = base + lane;
-        bool fresh = false;
-        if (i < hi) {
-          const uint32_t pi = (uint32_t)p[i], ci = (uint32_t)c[i], ti = (uint32_t)tenant[i];
-          const uint64_t pp = (uint64_t)pi * pi;
-          const uint64_t pc = (uint64_t)pi * ci;
-          if (!WRITE) {
-            sp += pi;
-            sc += ci;
-            sz += ci == 0 ? 1u : 0u;
-            sq += pp;
-            if (EXT) sr += pc;
-          }
-          uint32_t h = grp_hash(ti);
-          while (true) {  // ends: fewer than kGrpSlots keys are ever held
-            const uint32_t old = atomicCAS(&H.key[h], kGrpEmpty, ti);
-            if (old == kGrpEmpty) {
-              fresh = true;
-              break;
-            }
-            if (old == ti) break;
-            h = (h + 1) & (kGrpSlots - 1);
-          }
-          if (WRITE) {
-            atomicAdd(&H.n[h], 1u);
-            atomicAdd(&H.p[h], (unsigned long long)pi);
-            atomicAdd(&H.c[h], (unsigned long long)ci);
-            atomicAdd(&H.q[h], (unsigned long long)pp);
-            if (EXT) atomicAdd(&H.r[h], (unsigned long long)pc);
-          }
-        }
-        taken += __builtin_popcountll(__ballot(fresh));
-        wave_lds_sync();
-        if (taken > kGrpFlush || base + 64 >= hi) {
-          // emit the held groups in slot order, clearing their slots
-#pragma unroll
-          for (int j = 0; j < kGrpSlots / 64; ++j) {
-            const int s = j * 64 + lane;
-            const uint32_t key = H.key[s];
-            const bool used = key != kGrpEmpty;
-            const uint64_t m = __ballot(used);
-            if (used) {
-              if (WRITE) {
-                const int64_t at = out + __builtin_popcountll(m & ((1ull << lane) - 1ull));
-                gw[at] = (((uint32_t)b & kGrpBatchMask) << kGrpTenantBits) | key;
-                gf[at] = (v4f){(float)H.n[s], (float)H.p[s], (float)H.c[s], (float)H.q[s]};
-                if (EXT) {
-                  gr[at] = (float)H.r[s];
-                  H.r[s] = 0;
-                }
-                H.n[s] = 0;
-                H.p[s] = 0;
-                H.c[s] = 0;
-                H.q[s] = 0;
-              }
-              H.key[s] = kGrpEmpty;
-            }
-            out += __builtin_popcountll(m);
-          }
-          taken = 0;
-          wave_lds_sync();
-        }
-      }
-      if (!WRITE) {
-        sp = wave_sum(sp);
-        sc = wave_sum(sc);
-        sq = wave_sum(sq);
-        sz = wave_sum(sz);
-        if (EXT) sr = wave_sum(sr);
-        if (lane == 0) {
-          if (bo0 >= r0 && bo1 <= r1) {  // the whole batch
-            bsum[b] = sp;
-            bsum[nB + b] = sc;
-            bsum[2 * nB + b] = sq;
-            bsum[3 * nB + b] = sz;
-            if (EXT) bsum[4 * nB + b] = sr;
-          } else {
-            atomicAdd(&bsum[b], (unsigned long long)sp);
-            atomicAdd(&bsum[nB + b], (unsigned long long)sc);
-            atomicAdd(&bsum[2 * nB + b], (unsigned long long)sq);
-            atomicAdd(&bsum[3 * nB + b], (unsigned long long)sz);
-            if (EXT) atomicAdd(&bsum[4 * nB + b], (unsigned long long)sr);
-          }
-        }
-      }
-    }
-    if (!WRITE && lane == 0) slice_cnt[k] = out;
-    if (WRITE && last && lane == 0) gofs[nB] = out;
-  }
-}
-
-// ------------------------------------------------------------ offsets scan
-
-constexpr int kScanWG = 1024;
-constexpr int kScanPer = 8;
-constexpr int64_t kScanTile = (int64_t)kScanWG * kScanPer;
-
-// Exclusive scan of one value per thread over the workgroup; *total gets
-// the sum.  Every thread of the workgroup calls it.
-__device__ __forceinline__ int64_t block_excl_scan(int64_t v, int64_t* total) {
-  __shared__ int64_t s_w[kScanWG / 64];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  int64_t x = v;
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const int64_t y = __shfl_up(x, d, 64);
-    if (lane >= d) x += y;
-  }
-  if (lane == 63) s_w[w] = x;
+  for (int u = tid; u < 2 * T; u += kWG)
+    s_cur[u] = cells[(int64_t)blockIdx.x * 2 * T + u];
   __syncthreads();
-  int64_t before = 0, tot = 0;
-  for (int k = 0; k < kScanWG / 64; ++k) {
-    const int64_t t = s_w[k];
-    before += k < w ? t : 0;
-    tot += t;
+  int32_t open = 0;
+  const int64_t k1 = slice_lo(nS, blockIdx.x + 1, gridDim.x);
+  for (int64_t k = slice_lo(nS, blockIdx.x, gridDim.x) + wave; k < k1; k += kWaves) {
+    const int64_t r0 = k * slice;
+    const int32_t* const src[3] = {tenant, p, c};
+    walk_slice<3>(off, nrow, nB, r0, min(N, r0 + slice), uni(first[k]), src, s_win[wave],
+                  [&](int32_t j0, int32_t cnt, int, int64_t) {
+      bool fresh = false;
+      uint32_t h = 0;
+      if (lane < cnt) {
+        const uint32_t ti = (uint32_t)s_win[wave][0][j0 + lane];
+        const uint32_t pi = (uint32_t)s_win[wave][1][j0 + lane];
+        const uint32_t ci = (uint32_t)s_win[wave][2][j0 + lane];
+        h = grp_hash(ti);
+        while (true) {  // ends: fewer than kGrpSlots keys are ever held
+          const uint32_t old = atomicCAS(&H.key[h], kGrpEmpty, ti);
+          if (old == kGrpEmpty) {
+            fresh = true;
+            break;
+          }
+          if (old == ti) break;
+          h = (h + 1) & (kGrpSlots - 1);
+        }
+        atomicAdd(&H.n[h], 1u);
+        atomicAdd(&H.p[h], (unsigned long long)pi);
+        atomicAdd(&H.c[h], (unsigned long long)ci);
+        atomicAdd(&H.q[h], (unsigned long long)pi * pi);
+        if (EXT) atomicAdd(&H.r[h], (unsigned long long)pi * ci);
+      }
+      const uint64_t m = __ballot(fresh);
+      if (fresh) H.slot[open + __builtin_popcountll(m & ((1ull << lane) - 1ull))] = (uint8_t)h;
+      open += __builtin_popcountll(m);
+      return (int32_t)__builtin_popcountll(m);
+    }, [&](int phase, int64_t b, int32_t n_open) {
+      wave_lds_sync();
+      for (int32_t i = lane; i < n_open; i += 64) {
+        const int s = H.slot[i];
+        const uint32_t t = H.key[s];
+        const int64_t at = base[2 * t + phase] + atomicAdd(&s_cur[2 * t + phase], 1u);
+        Group<EXT> g;
+        g.b = (uint32_t)b;
+        g.nb = H.n[s] | ((uint32_t)(b >> 32) << kNBits);
+        g.s[0] = (float)H.p[s];
+        g.s[1] = (float)H.c[s];
+        g.s[2] = (float)H.q[s];
+        if constexpr (EXT) {
+          g.s[3] = (float)H.r[s];
+          H.r[s] = 0;
+        }
+        out[at] = g;
+        H.key[s] = kGrpEmpty;
+        H.n[s] = 0;
+        H.p[s] = H.c[s] = H.q[s] = 0;
+      }
+      open = 0;
+      wave_lds_sync();
+    });
   }
-  __syncthreads();
-  *total = tot;
-  return before + x - v;
 }
 
-// tile_sum[t] = sum of x over tile t (kScanTile elements).
-__global__ __launch_bounds__(kScanWG) void k_scan_tiles(const int64_t* __restrict__ x, int64_t n,
-                                                         int64_t* __restrict__ tile_sum) {
-  const int64_t i0 = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanPer;
-  int64_t s = 0;
-  for (int k = 0; k < kScanPer; ++k) s += i0 + k < n ? x[i0 + k] : 0;
-  int64_t tot = 0;
-  block_excl_scan(s, &tot);
-  if (threadIdx.x == 0) tile_sum[blockIdx.x] = tot;
-}
+// ------------------------------------------------------------ settings
 
-// One workgroup: exclusive scan of the nt tile sums, in place.
-__global__ __launch_bounds__(kScanWG) void k_scan_top(int64_t* __restrict__ t, int64_t nt) {
-  int64_t carry = 0;
-  for (int64_t base = 0; base < nt; base += kScanTile) {
-    const int64_t i0 = base + (int64_t)threadIdx.x * kScanPer;
-    int64_t v[kScanPer], s = 0;
-    for (int k = 0; k < kScanPer; ++k) {
-      v[k] = i0 + k < nt ? t[i0 + k] : 0;
-      s += v[k];
-    }
-    int64_t tot = 0;
-    int64_t e = block_excl_scan(s, &tot) + carry;
-    for (int k = 0; k < kScanPer; ++k) {
-      if (i0 + k < nt) t[i0 + k] = e;
-      e += v[k];
-    }
-    carry += tot;
-  }
-}
-
-// y[i] = sum of x[0..i) for i <= n (y has n + 1 entries); tile_off from
-// k_scan_tiles and k_scan_top.
-__global__ __launch_bounds__(kScanWG) void k_scan_apply(const int64_t* __restrict__ x, int64_t n,
-                                                         const int64_t* __restrict__ tile_off,
-                                                         int64_t* __restrict__ y) {
-  const int64_t i0 = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanPer;
-  int64_t v[kScanPer], s = 0;
-  for (int k = 0; k < kScanPer; ++k) {
-    v[k] = i0 + k < n ? x[i0 + k] : 0;
-    s += v[k];
-  }
-  int64_t tot = 0;
-  int64_t e = block_excl_scan(s, &tot) + tile_off[blockIdx.x];
-  for (int k = 0; k < kScanPer; ++k) {
-    if (i0 + k < n) y[i0 + k] = e;
-    e += v[k];
-    if (i0 + k == n - 1) y[n] = e;
-  }
-  if (n == 0 && blockIdx.x == 0 && threadIdx.x == 0) y[0] = 0;
-}
-
-// ------------------------------------------------------------ sweep pass
-
-constexpr int kGV = 16;                    // group slots per lane of a sweep tile
-constexpr int kGT = 64 * kGV;              // group slots per sweep tile
-// batches per sweep tile: the per-wave constant tables of 8 settings then
-// leave room for two workgroups per CU beside 8 histograms of 1040 entries
-template <int NC> constexpr int kGBof = NC == 5 ? 28 : 22;
-static_assert(kGV % 4 == 0 && kGBof<5> < 64 && kGBof<7> < 64, "sweep tile shape");
-
-struct GroupSweep {
-  const int64_t* off;               // request offsets [nB + 1]
-  const int64_t* gofs;              // group offsets [nB + 1]
-  const unsigned long long* bsum;   // [4][nB]: sum p, sum c, sum p^2, count of c == 0;
-                                    // [5][nB] with sum p*c (extended model)
-  const uint32_t* gw;               // [groups + kGT] ((b mod 2^20) << 12) | tenant
-  const v4f* gf;                    // [groups + kGT] (n, P, C, Q)
-  const float* gr;                  // [groups + kGT] R = sum p*c (extended model)
-  int64_t nB;
-  const int64_t* wg_first;          // chunk table over batches (k_partition)
-  unsigned long long* claims;
-  int64_t n_chunks;
-  uint64_t claim_base;
-  double* partials;                 // [grid][V.n][n_tenants]
-  int32_t n_tenants;
-  const int32_t* hot;               // [kHot]
-  // the previous pass's partials ([gridDim.x][prev_n][n_tenants], the other
-  // buffer), folded into its output rows by this pass (null: none)
-  const double* prev;
-  double* prev_out;
-  int32_t prev_n;
+// Setting v of a call = (shape v / n_coeffs, coefficient vector v %
+// n_coeffs).  A round evaluates the n settings from v0 on; the coefficient
+// vectors jbase.. are held on the device (raw, fp32).
+struct Settings {
+  const float* raw;     // [vectors held][4*NC]
+  const double* S;      // [n_shapes][6]: S0..S3 (and S5, S6)
+  int64_t n_coeffs, jbase, v0;
+  int32_t n;            // settings of the round
+  int32_t ld;           // columns of table, mask blocks * 64
+  double* table;        // [kSweepRows][ld]: theta*S of the sums' features
+  double* diff;         // [2][64][8]: COMP minus MEM of them, prefill and decode, by setting
 };
 
-// Fold of the previous pass inside a pass: workgroup w owns entries
-// [w*kFoldPer, (w+1)*kFoldPer) of the prev_n*n_tenants sums; thread t holds
-// entry t % kFoldPer and rows t/kFoldPer + kFoldGroups*k, k < kFoldRows, loaded
-// at the start of the pass and added after its own work (rows in a fixed
-// order).  Used when prev_n*n_tenants <= kFoldPer*gridDim.x and gridDim.x <=
-// kFoldGroups*kFoldRows.
-constexpr int kFoldPer = 32;
-constexpr int kFoldGroups = 16;  // kSweepWG / kFoldPer
-constexpr int kFoldRows = 16;
+constexpr int kSweepRound = 1024;  // settings per round, at most
+constexpr int kSweepShapes = 64;   // shapes per call, at most
 
-// Threads per sweep workgroup: eight waves share one set of NV tenant
-// histograms (one workgroup per compute unit), so a pass writes half as many
-// partial rows as with four-wave workgroups.
-constexpr int kSweepWG = 512;
-constexpr int kSweepWaves = kSweepWG / 64;
-static_assert(kSweepWG == 16 * 32, "the fold's thread mapping");
+// Host arrays travel as kernel arguments (under 4 KiB each), so that a call
+// can be captured and needs no host memory after it returns.
+struct ShapeArgs {
+  double S[kSweepShapes][6];
+};
+constexpr int kPutWords = 960;
+struct CoeffArgs {
+  float c[kPutWords];
+};
+static_assert(sizeof(ShapeArgs) + 32 < 4096 && sizeof(CoeffArgs) + 32 < 4096, "kernel arguments");
 
-// NV: histogram rows, i.e. settings per pass, >= V.n; NC: 5 (Eq. 1) or 7
-// (the extended model).  Work: the chunks of k_tiles (one static chunk per
-// wave, then claimed ones).  LDS per workgroup: NV * (n_tenants + kHotSlots)
-// doubles (dynamic) plus the per-wave tables.
-template <int NV, int NC>
-__global__ __launch_bounds__(kSweepWG) void k_sweep_groups(const GroupSweep P, const VarTableOf<NC> V) {
-  constexpr bool EXT = NC == 7;
-  constexpr int kGB = kGBof<NC>;
-  constexpr int KC = EXT ? 4 : 3;                    // batch-independent constants
-#ifndef LLMV_SWEEP_PRE
-#define LLMV_SWEEP_PRE 1
-#endif
-  constexpr bool PRE = LLMV_SWEEP_PRE && !(EXT && NV == 4);  // registers: no spills
-  extern __shared__ double s_hist[];                 // [NV][n_tenants + kHotSlots]
-  __shared__ v4f s_kt[kSweepWaves][NV][kGB];              // per wave: (k0, k1, k2, k3)
-  __shared__ float s_kt5[kSweepWaves][EXT ? NV : 1][EXT ? kGB : 1];  // per wave: k5
-  __shared__ float s_K[NV * 4 * KC];                 // [setting][regime][k1..k3 (, k5)]
-  __shared__ double s_fold[kSweepWG];                // the fold's row groups
-  const int tid = threadIdx.x, lane = tid & 63;
-  // [setting][batch of the tile]: lanes of one read that hold different
-  // batches fall in different banks
-  v4f(*kt)[kGB] = s_kt[tid >> 6];
-  float(*kt5)[EXT ? kGB : 1] = s_kt5[tid >> 6];
-  const int32_t T = P.n_tenants, TS = T + kHotSlots;
-  int32_t hot[kHot];
+__global__ __launch_bounds__(64) void k_put_shapes(const ShapeArgs A, int n, double* __restrict__ S) {
+  for (int i = threadIdx.x; i < n * 6; i += 64) S[i] = A.S[i / 6][i % 6];
+}
+
+__global__ __launch_bounds__(256) void k_put_coeffs(const CoeffArgs A, int n, float* __restrict__ c) {
+  for (int i = threadIdx.x; i < n; i += 256) c[i] = A.c[i];
+}
+
+// Features of a group's sums, in the order the sum kernel holds them, and the
+// rows of `table` (theta*S) they pair with:
+//   prefill: n/|B|, P, C, n*|B|, Q (and R, n): kPre rows per segment
+//   decode:  n/|B|, n, C, n*|B| (every p is 1: P = Q = n, R = C)
+constexpr int kDecFeatures = 4;
+template <int NC> constexpr int kPreFeatures = NC;
+// table rows: prefill MEM, prefill COMP, decode MEM, decode COMP
+template <int NC> constexpr int kSweepRows = 2 * kPreFeatures<NC> + 2 * kDecFeatures;
+
+// mask[(g*nB + b)*NBLK + q] bit l: setting v0 + (g*NBLK + q)*64 + l makes
+// batch b compute-bound (T_COMP > T_MEM strictly, as in MODE_ATTR and
+// MODE_EXT: the same fp64 operations in the same order).  A wave takes one
+// block of 64 settings (lane l one setting) and `per` batches, 64 at a time:
+// their sums go through LDS, each batch's 64 segment bits are one ballot.
+// Bound by its fp64 operations, about 23 per batch and 64 settings.
+template <int NC>
+__global__ __launch_bounds__(kWG) void k_sweep_mask(const int64_t* __restrict__ bsum, int64_t nB,
+                                                    const Settings V, int per, int NBLK,
+                                                    uint64_t* __restrict__ mask) {
+  constexpr int NX = NC == 7 ? 5 : 4;
+  __shared__ double s_x[kWaves][64][6];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int blk = blockIdx.y, g = blk / NBLK, q = blk % NBLK;
+  const int64_t v = V.v0 + min(blk * 64 + lane, V.n - 1);
+  const float* c = V.raw + (v % V.n_coeffs - V.jbase) * 4 * NC;
+  const double* Sv = V.S + (v / V.n_coeffs) * 6;
+  double th[4][NC], S[6];
 #pragma unroll
-  for (int h = 0; h < kHot; ++h) hot[h] = uni(P.hot[h]);
-  for (int i = tid; i < NV * 4 * KC; i += kSweepWG)
-    s_K[i] = V.K[i / (4 * KC)][(i / KC) % 4][i % KC];
-  // the previous pass's partials of this workgroup's entries, loaded now and
-  // folded after this pass's own work
-  const int64_t fe = (int64_t)blockIdx.x * kFoldPer + tid % kFoldPer;
-  const int frg = tid / kFoldPer;
-  const int64_t fE = (int64_t)P.prev_n * T;
-  double fr[kFoldRows];
+  for (int i = 0; i < 6; ++i) S[i] = Sv[i];
 #pragma unroll
-  for (int k = 0; k < kFoldRows; ++k) {
-    const int row = frg + kFoldGroups * k;
-    fr[k] = (P.prev && fe < fE && row < (int)gridDim.x) ? P.prev[(int64_t)row * fE + fe] : 0.0;
-  }
-  for (int u = tid; u < NV * TS; u += kSweepWG) s_hist[u] = 0.0;
-  __syncthreads();
-
-  const int64_t workers = (int64_t)gridDim.x * kSweepWaves;
-  int64_t chunk = (int64_t)blockIdx.x * kSweepWaves + (tid >> 6);
-  while (chunk < P.n_chunks) {
-    // claim the next chunk now: the value is first read once this one is done
-    unsigned long long claim = ~0ull;
-    if (P.n_chunks > workers && lane == 0) claim = atomicAdd(P.claims, 1ull);
-    const int64_t bw0 = uni(P.wg_first[chunk]), bw1 = uni(P.wg_first[chunk + 1]);
-    int64_t b = bw0;
-    while (b < bw1) {
-      // ---- tile: the longest run of whole batches from b within kGT group
-      // slots from a 4-aligned base, at most kGB batches; a batch with more
-      // groups alone, in several rounds
-      const int64_t lim = min((int64_t)kGB, bw1 - b);
-      const int64_t gv = lane <= lim ? P.gofs[b + lane] : 0;  // lane j: gofs[b + j]
-      const int64_t g0 = uni(readlane_i64(gv, 0));
-      const int64_t ga = g0 & ~(int64_t)3;
-      const uint64_t fits = __ballot(lane >= 1 && lane <= lim && gv - ga <= kGT);
-      int32_t count = uni((int32_t)__builtin_popcountll(fits));  // a prefix of lanes
-      if (count == 0) count = 1;
-      const int64_t g1 = uni(readlane_i64(gv, count));
-
-      // ---- lane j: batch b + j under every setting
-      if (lane < count) {
-        const int64_t bb = b + lane;
-        const int64_t n = P.off[bb + 1] - P.off[bb];
-        if (n > 0) {
-          const uint64_t sp = P.bsum[bb], sc = P.bsum[P.nB + bb], sq = P.bsum[2 * P.nB + bb];
-          const uint64_t sz = P.bsum[3 * P.nB + bb];
-          const uint64_t sr = EXT ? P.bsum[4 * P.nB + bb] : 0;
-          // decode iff every request processes one token over a nonzero context
-          const bool prefill = (sp != (uint64_t)n) || (sz != 0);
-          float k0[kSweepG];
-          const uint32_t sg = sweep_batch<NV, NC>(V, n, sp, sc, sq, sr, prefill, k0);
-          const int ph = prefill ? 0 : 1;
+  for (int r = 0; r < 4; ++r)
 #pragma unroll
-          for (int g = 0; g < NV; ++g) {
-            const int r = 2 * ph + (int)((sg >> g) & 1u);
-            const float* kr = &s_K[(g * 4 + r) * KC];
-            kt[g][lane] = (v4f){k0[g], kr[0], kr[1], kr[2]};
-            if (EXT) kt5[g][lane] = kr[KC - 1];
-          }
-        }
+    for (int k = 0; k < NC; ++k) th[r][k] = (double)c[r * NC + k];
+  if (blockIdx.x == 0 && wave == 0) {
+    double* t = V.table + blk * 64 + lane;
+    auto put = [&](int row, double x) { t[(int64_t)row * V.ld] = x; };
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      const int pr = s * kPreFeatures<NC>, dr = 2 * kPreFeatures<NC> + s * kDecFeatures;
+      put(pr + 0, th[s][0] * S[0]);
+      put(pr + 1, th[s][1] * S[1]);
+      put(pr + 2, th[s][2] * S[2]);
+      put(pr + 3, th[s][4]);
+      put(pr + 4, th[s][3] * S[3]);
+      const double* d = th[2 + s];
+      double dn = d[1] * S[1] + d[3] * S[3], dc = d[2] * S[2];
+      if constexpr (NC == 7) {
+        put(pr + 5, th[s][5] * S[4]);
+        put(pr + 6, th[s][6] * S[5]);
+        dn += d[6] * S[5];
+        dc += d[5] * S[4];
       }
-      wave_lds_sync();
-
-      // ---- groups: lane-local runs of kGV slots; a lane reloads its
-      // constants when its batch changes
-      for (int64_t base = ga; base < g1; base += kGT) {
-        const int64_t x = base + (int64_t)lane * kGV;
-        uint32_t wv[kGV];
-        v4f fv[kGV];
-        float rv[EXT ? kGV : 1];
-        // (x is a multiple of 4; the group arrays hold kGT slots past the last group)
-#pragma unroll
-        for (int v = 0; v < kGV / 4; ++v) {
-          const v4i a = *(const v4i*)(P.gw + x + 4 * v);
-          wv[4 * v] = (uint32_t)a.x;
-          wv[4 * v + 1] = (uint32_t)a.y;
-          wv[4 * v + 2] = (uint32_t)a.z;
-          wv[4 * v + 3] = (uint32_t)a.w;
-        }
-#pragma unroll
-        for (int q = 0; q < kGV; ++q) fv[q] = P.gf[x + q];
-        if constexpr (EXT) {
-#pragma unroll
-          for (int v = 0; v < kGV / 4; ++v) {
-            const v4f a = *(const v4f*)(P.gr + x + 4 * v);
-            rv[4 * v] = a.x;
-            rv[4 * v + 1] = a.y;
-            rv[4 * v + 2] = a.z;
-            rv[4 * v + 3] = a.w;
-          }
-        }
-        uint32_t kcur = 0xffffffffu;
-        v4f K[NV];
-        float K5[EXT ? NV : 1];
-        // PRE: the constants of the batch of the lane's first slot and of
-        // the batch after it are read before the first atomic: a read
-        // between the atomics waits for every atomic before it (LDS
-        // operations of a wave complete in order)
-        v4f KB[PRE ? NV : 1];
-        float KB5[PRE && EXT ? NV : 1];
-        uint32_t kbi = 0xffffffffu;
-        if constexpr (PRE) {
-          uint32_t l0 = ((wv[0] >> kGrpTenantBits) - (uint32_t)b) & kGrpBatchMask;
-          l0 = min(l0, (uint32_t)count - 1u);  // slots before the tile's first group: any batch
-          kcur = l0;
-#pragma unroll
-          for (int g = 0; g < NV; ++g) {
-            K[g] = kt[g][l0];
-            if (EXT) K5[g] = kt5[g][l0];
-          }
-          if (l0 + 1u < (uint32_t)count) {
-            kbi = l0 + 1u;
-#pragma unroll
-            for (int g = 0; g < NV; ++g) {
-              KB[g] = kt[g][kbi];
-              if (EXT) KB5[g] = kt5[g][kbi];
-            }
-          }
-        }
-#pragma unroll
-        for (int q = 0; q < kGV; ++q) {
-          if (x + q >= g0 && x + q < g1) {
-            const uint32_t w = wv[q];
-            const uint32_t lb = ((w >> kGrpTenantBits) - (uint32_t)b) & kGrpBatchMask;
-            const int32_t t = (int32_t)(w & kGrpTenantMask);
-            int32_t e = t;
-#pragma unroll
-            for (int h = 0; h < kHot; ++h)
-              if (t == hot[h]) e = T + h * kHotRep + (lane & (kHotRep - 1));
-            if (lb != kcur) {
-              kcur = lb;
-              if (PRE && lb == kbi) {
-#pragma unroll
-                for (int g = 0; g < NV; ++g) {
-                  K[g] = KB[g];
-                  if (EXT) K5[g] = KB5[g];
-                }
-              } else {
-#pragma unroll
-                for (int g = 0; g < NV; ++g) {
-                  K[g] = kt[g][lb];
-                  if (EXT) K5[g] = kt5[g][lb];
-                }
-              }
-            }
-            const v4f f = fv[q];
-            // all NV rows: rows past V.n are scratch, never flushed
-#pragma unroll
-            for (int g = 0; g < NV; ++g) {
-              float t = fmaf(K[g].w, f.w, fmaf(K[g].z, f.z, fmaf(K[g].y, f.y, K[g].x * f.x)));
-              if constexpr (EXT) t = fmaf(K5[g], rv[q], t);
-              atomicAdd(s_hist + g * TS + e, (double)t);
-            }
-          }
-        }
-      }
-      wave_lds_sync();
-      b += count;
+      put(dr + 0, d[0] * S[0]);
+      put(dr + 1, dn);
+      put(dr + 2, dc);
+      put(dr + 3, d[4]);
     }
-    // claim k of this launch names chunk workers + k; past the last chunk, stop
-    const uint64_t k = readlane_u64((uint64_t)claim, 0) - P.claim_base;
-    chunk = k < (uint64_t)(P.n_chunks - workers) ? workers + (int64_t)k : P.n_chunks;
-  }
-
-  // fold the hot tenants' replicas (fixed order), then flush n_tenants
-  // entries per setting
-  __syncthreads();
-  for (int i = tid; i < V.n * kHot; i += kSweepWG) {
-    const int g = i / kHot, h = i % kHot;
-    if (hot[h] >= 0) {
-      double acc = s_hist[g * TS + hot[h]];
-      for (int r = 0; r < kHotRep; ++r) acc += s_hist[g * TS + T + h * kHotRep + r];
-      s_hist[g * TS + hot[h]] = acc;
+    if (blk == 0) {  // for k_sweep_few
+      for (int k = 0; k < kPreFeatures<NC>; ++k)
+        V.diff[lane * 8 + k] = t[(int64_t)(kPreFeatures<NC> + k) * V.ld] - t[(int64_t)k * V.ld];
+      for (int k = 0; k < kDecFeatures; ++k)
+        V.diff[(64 + lane) * 8 + k] = t[(int64_t)(2 * kPreFeatures<NC> + kDecFeatures + k) * V.ld] -
+                                      t[(int64_t)(2 * kPreFeatures<NC> + k) * V.ld];
     }
   }
-  __syncthreads();
-  double* dst = P.partials + (int64_t)blockIdx.x * V.n * T;
-  for (int i = tid; i < V.n * T; i += kSweepWG) dst[i] = s_hist[(i / T) * TS + i % T];
-
-  // the fold: each thread's rows in order, then the row groups in order
-  if (P.prev) {
-    double acc = fr[0];
+  const int64_t b1 = min(nB, ((int64_t)blockIdx.x * kWaves + wave + 1) * per);
+  for (int64_t b0 = ((int64_t)blockIdx.x * kWaves + wave) * per; b0 < b1; b0 += 64) {
+    const int64_t b = b0 + lane;
+    bool pre = false;
+    if (b < b1) {
+      const int64_t n0 = bsum[b], n = n0 & kSizeMask;
+      pre = (n0 & kPrefillBit) != 0;
+      s_x[wave][lane][0] = (double)(uint64_t)bsum[nB + b];
+      s_x[wave][lane][1] = (double)(uint64_t)bsum[2 * nB + b];
+      s_x[wave][lane][2] = (double)(uint64_t)bsum[3 * nB + b];
+      s_x[wave][lane][3] = (double)n * (double)n;
+      if constexpr (NX == 5) {
+        s_x[wave][lane][4] = (double)(uint64_t)bsum[4 * nB + b];
+        s_x[wave][lane][5] = (double)n;
+      }
+    }
+    const uint64_t pres = __ballot(pre);
+    wave_lds_sync();
+    const uint64_t in = __ballot(b < b1);
+    uint32_t lo = 0, hi = 0;
+    auto value = [&](const double* t, const double* X) {
+      double acc = t[0] * S[0];
 #pragma unroll
-    for (int k = 1; k < kFoldRows; ++k) acc += fr[k];
-    s_fold[frg * kFoldPer + tid % kFoldPer] = acc;
+      for (int k = 1; k < NC; ++k) acc = acc + t[k] * X[k];
+      return acc;
+    };
+    // the batches of one phase, under its two coefficient sets
+    auto phase = [&](uint64_t todo, const double* tm, const double* tc) {
+      while (todo) {
+        const int i = __builtin_ctzll(todo);
+        todo &= todo - 1;
+        const double* x = s_x[wave][i];
+        double X[NC];
+        X[1] = S[1] * x[0];
+        X[2] = S[2] * x[1];
+        X[3] = S[3] * x[2];
+        X[4] = x[3];
+        if constexpr (NC == 7) {
+          X[5] = S[4] * x[4];
+          X[6] = S[5] * x[5];
+        }
+        const uint64_t m = __ballot(value(tc, X) > value(tm, X));
+        if (lane == i) {
+          lo = (uint32_t)m;
+          hi = (uint32_t)(m >> 32);
+        }
+      }
+    };
+    phase(in & pres, th[0], th[1]);
+    phase(in & ~pres, th[2], th[3]);
+    if (b < b1) mask[((int64_t)g * nB + b) * NBLK + q] = ((uint64_t)hi << 32) | lo;
+    wave_lds_sync();
+  }
+}
+
+// ------------------------------------------------------------ the sums
+
+constexpr int kSumTile = 256;      // groups staged per workgroup step
+constexpr int kSumMinChunk = 64;   // groups per chunk, at least
+constexpr int kSumChunks = 3072;   // chunks, at most
+
+struct SweepSum {
+  const int64_t* base;      // [2T + 1] first group of each bin
+  const void* groups;       // Group<NC == 7>, sorted by bin (k_group_emit)
+  const int64_t* nrow;      // |B| and the phase bit
+  const uint64_t* mask;     // k_sweep_mask
+  const double* table;      // [kSweepRows][ld]
+  const double* diff;       // Settings::diff
+  double* part;             // [chunks + 2T][ld]
+  int64_t nB;
+  int32_t bins;             // 2T
+  int32_t ld;
+  int32_t big;              // large chunks (SumChunks)
+  int32_t WS;               // waves side by side over the settings (1, 2): ld = WS*NBLK*64
+};
+
+// The bin holding group g: the last one starting at or before it.
+__device__ __forceinline__ int bin_of(const int64_t* __restrict__ base, int bins, int64_t g) {
+  int lo = 0, hi = bins - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (base[mid] <= g) lo = mid;
+    else hi = mid - 1;
+  }
+  return lo;
+}
+
+// A group's features (kPreFeatures of them; of a decode group only the first
+// kDecFeatures are meant) in a batch of B requests.
+template <int NC>
+__device__ __forceinline__ void group_features(const Group<NC == 7>& g, double B, bool dec,
+                                               double* f) {
+  const double n = (double)(g.nb & ((1u << kNBits) - 1u));
+  f[0] = n / B;
+  f[1] = dec ? n : (double)g.s[0];
+  f[2] = (double)g.s[1];
+  f[3] = n * B;
+  f[4] = (double)g.s[2];
+  if constexpr (NC == 7) {
+    f[5] = (double)g.s[3];
+    f[6] = n;
+  }
+}
+
+// Workgroups per compute unit (waves per SIMD) that the registers allow
+// without spills.
+template <int NC, int NBLK> constexpr int kSumWaves = NC == 7 && NBLK != 4 ? 2 : 3;
+
+// The sorted groups are cut into `big` large chunks (7/10 of the groups, one
+// per workgroup that is resident at once) and chunks - big small ones, which
+// start as the large ones end: groups of the two phases cost differently, and
+// with equal chunks a quarter of the wave slots stood empty at the end.
+struct SumChunks {
+  int64_t groups, cb, cs;
+  int big;
+  __device__ SumChunks(int64_t n, int chunks, int big_) : groups(n), big(big_) {
+    const int64_t part = chunks > big ? n / 10 * 7 : n;
+    cb = max((part + big - 1) / big, (int64_t)kSumMinChunk);
+    const int64_t rest = max(n - cb * big, (int64_t)0);
+    const int small = max(chunks - big, 1);
+    cs = max((rest + small - 1) / small, (int64_t)kSumMinChunk);
+  }
+  __device__ int64_t start(int i) const {
+    return min(groups, i <= big ? cb * i : cb * big + cs * (i - big));
+  }
+  __device__ int64_t owner(int64_t g) const {
+    return g < cb * big ? g / cb : big + (g - cb * big) / cs;
+  }
+};
+
+// a[q][k] += f[k], k < NF, in the lanes of m[q], q < NB: fp64 adds under the
+// exec mask, restored at the end (the wave is whole here).  A select or a
+// multiplication by 0 or 1 per mask would be one more vector instruction
+// beside every NF adds (the sum kernel of the what-if workload 1.47 against
+// 1.24 ms); the mask moves are scalar and issue beside another wave's adds.
+#define LLMV_ADD(a, f) "v_add_f64 %" #a ", %" #a ", %" #f "\n\t"
+#define LLMV_ACC4(q) "+v"(a[q][0]), "+v"(a[q][1]), "+v"(a[q][2]), "+v"(a[q][3])
+#define LLMV_ACC5(q) LLMV_ACC4(q), "+v"(a[q][4])
+#define LLMV_ACC7(q) LLMV_ACC5(q), "+v"(a[q][5]), "+v"(a[q][6])
+#define LLMV_IN4 "v"(f[0]), "v"(f[1]), "v"(f[2]), "v"(f[3])
+#define LLMV_IN5 LLMV_IN4, "v"(f[4])
+#define LLMV_IN7 LLMV_IN5, "v"(f[5]), "v"(f[6])
+template <int NF, int NB, int NP>
+__device__ __forceinline__ void add_masked(double (*a)[NP], const double* f, const uint64_t* m) {
+  static_assert((NF == 4 || NF == 5 || NF == 7) && (NB == 1 || NB == 4), "written out below");
+  uint64_t all;
+  if constexpr (NF == 4 && NB == 1) {
+    asm("s_and_saveexec_b64 %4, %9\n\t" LLMV_ADD(0, 5) LLMV_ADD(1, 6) LLMV_ADD(2, 7) LLMV_ADD(3, 8)
+        "s_mov_b64 exec, %4"
+        : LLMV_ACC4(0), "=&s"(all)
+        : LLMV_IN4, "s"(m[0])
+        : "scc");
+  } else if constexpr (NF == 4 && NB == 4) {
+    asm("s_and_saveexec_b64 %16, %21\n\t" LLMV_ADD(0, 17) LLMV_ADD(1, 18) LLMV_ADD(2, 19) LLMV_ADD(3, 20)
+        "s_and_b64 exec, %16, %22\n\t" LLMV_ADD(4, 17) LLMV_ADD(5, 18) LLMV_ADD(6, 19) LLMV_ADD(7, 20)
+        "s_and_b64 exec, %16, %23\n\t" LLMV_ADD(8, 17) LLMV_ADD(9, 18) LLMV_ADD(10, 19) LLMV_ADD(11, 20)
+        "s_and_b64 exec, %16, %24\n\t" LLMV_ADD(12, 17) LLMV_ADD(13, 18) LLMV_ADD(14, 19) LLMV_ADD(15, 20)
+        "s_mov_b64 exec, %16"
+        : LLMV_ACC4(0), LLMV_ACC4(1), LLMV_ACC4(2), LLMV_ACC4(3), "=&s"(all)
+        : LLMV_IN4, "s"(m[0]), "s"(m[1]), "s"(m[2]), "s"(m[3])
+        : "scc");
+  } else if constexpr (NF == 5 && NB == 1) {
+    asm("s_and_saveexec_b64 %5, %11\n\t" LLMV_ADD(0, 6) LLMV_ADD(1, 7) LLMV_ADD(2, 8) LLMV_ADD(3, 9) LLMV_ADD(4, 10)
+        "s_mov_b64 exec, %5"
+        : LLMV_ACC5(0), "=&s"(all)
+        : LLMV_IN5, "s"(m[0])
+        : "scc");
+  } else if constexpr (NF == 5 && NB == 4) {
+    asm("s_and_saveexec_b64 %20, %26\n\t" LLMV_ADD(0, 21) LLMV_ADD(1, 22) LLMV_ADD(2, 23) LLMV_ADD(3, 24) LLMV_ADD(4, 25)
+        "s_and_b64 exec, %20, %27\n\t" LLMV_ADD(5, 21) LLMV_ADD(6, 22) LLMV_ADD(7, 23) LLMV_ADD(8, 24) LLMV_ADD(9, 25)
+        "s_and_b64 exec, %20, %28\n\t" LLMV_ADD(10, 21) LLMV_ADD(11, 22) LLMV_ADD(12, 23) LLMV_ADD(13, 24) LLMV_ADD(14, 25)
+        "s_and_b64 exec, %20, %29\n\t" LLMV_ADD(15, 21) LLMV_ADD(16, 22) LLMV_ADD(17, 23) LLMV_ADD(18, 24) LLMV_ADD(19, 25)
+        "s_mov_b64 exec, %20"
+        : LLMV_ACC5(0), LLMV_ACC5(1), LLMV_ACC5(2), LLMV_ACC5(3), "=&s"(all)
+        : LLMV_IN5, "s"(m[0]), "s"(m[1]), "s"(m[2]), "s"(m[3])
+        : "scc");
+  } else if constexpr (NF == 7 && NB == 1) {
+    asm("s_and_saveexec_b64 %7, %15\n\t" LLMV_ADD(0, 8) LLMV_ADD(1, 9) LLMV_ADD(2, 10) LLMV_ADD(3, 11) LLMV_ADD(4, 12) LLMV_ADD(5, 13) LLMV_ADD(6, 14)
+        "s_mov_b64 exec, %7"
+        : LLMV_ACC7(0), "=&s"(all)
+        : LLMV_IN7, "s"(m[0])
+        : "scc");
+  } else if constexpr (NF == 7 && NB == 4) {
+    asm("s_and_saveexec_b64 %28, %36\n\t" LLMV_ADD(0, 29) LLMV_ADD(1, 30) LLMV_ADD(2, 31) LLMV_ADD(3, 32) LLMV_ADD(4, 33) LLMV_ADD(5, 34) LLMV_ADD(6, 35)
+        "s_and_b64 exec, %28, %37\n\t" LLMV_ADD(7, 29) LLMV_ADD(8, 30) LLMV_ADD(9, 31) LLMV_ADD(10, 32) LLMV_ADD(11, 33) LLMV_ADD(12, 34) LLMV_ADD(13, 35)
+        "s_and_b64 exec, %28, %38\n\t" LLMV_ADD(14, 29) LLMV_ADD(15, 30) LLMV_ADD(16, 31) LLMV_ADD(17, 32) LLMV_ADD(18, 33) LLMV_ADD(19, 34) LLMV_ADD(20, 35)
+        "s_and_b64 exec, %28, %39\n\t" LLMV_ADD(21, 29) LLMV_ADD(22, 30) LLMV_ADD(23, 31) LLMV_ADD(24, 32) LLMV_ADD(25, 33) LLMV_ADD(26, 34) LLMV_ADD(27, 35)
+        "s_mov_b64 exec, %28"
+        : LLMV_ACC7(0), LLMV_ACC7(1), LLMV_ACC7(2), LLMV_ACC7(3), "=&s"(all)
+        : LLMV_IN7, "s"(m[0]), "s"(m[1]), "s"(m[2]), "s"(m[3])
+        : "scc");
+  }
+}
+#undef LLMV_ADD
+#undef LLMV_ACC4
+#undef LLMV_ACC5
+#undef LLMV_ACC7
+#undef LLMV_IN4
+#undef LLMV_IN5
+#undef LLMV_IN7
+
+// Workgroup i takes the i-th chunk of the sorted groups: runs of one bin
+// (one tenant and phase), each ending with one row of contributions, row i +
+// bin (no two (chunk, bin) pairs share a row: from one pair to the next either
+// grows).  The workgroup stages kSumTile groups' features in LDS as fp64; its
+// waves then split the settings (WS ways, 64*NBLK each) and the staged groups
+// (4/WS ways).  A wave reads a group's features as LDS broadcasts and its
+// segment mask with scalar loads, and adds the features under the mask: 4 or
+// NC fp64 adds per group and 64 settings.
+// Bound by those adds (the fp64 rate).
+template <int NC, int NBLK>
+__global__ __launch_bounds__(kWG, (kSumWaves<NC, NBLK>)) void k_sweep_sum(const SweepSum P) {
+  constexpr int NP = kPreFeatures<NC>, ND = kDecFeatures;
+  constexpr int FS = NC == 7 ? 8 : 6;  // feature stride: 16-byte aligned
+  __shared__ __align__(16) double s_f[kSumTile][FS];
+  __shared__ uint32_t s_lo[kSumTile], s_hi[kSumTile];
+  __shared__ double s_tot[kWaves][NP];
+  __shared__ double s_red[kWaves][NBLK * 64];
+  typedef const __attribute__((address_space(4))) uint64_t* MaskPtr;
+  const int tid = threadIdx.x, lane = tid & 63, wave = uni((int32_t)(tid >> 6));
+  const int ws = wave % P.WS, we = wave / P.WS, WE = kWaves / P.WS;
+  const SumChunks C(P.base[P.bins], gridDim.x, P.big);
+  const int64_t e0 = C.start(blockIdx.x), e1 = C.start(blockIdx.x + 1);
+  if (e0 >= e1) return;
+  int bin = bin_of(P.base, P.bins, e0);
+  const MaskPtr mask = (MaskPtr)(P.mask + (int64_t)ws * P.nB * NBLK);
+
+  double acc[NBLK][NP];
+  // Groups i0 .. i1-1 of the staged tile.  U groups' masks (scalar loads) and
+  // features (LDS broadcasts) are loaded while the U groups before them are
+  // added.  Scalar loads return in any order, so the wave can only wait for
+  // all of them: a step waits for the loads of the step before it, then issues
+  // the next ones, then adds.
+  auto tile = [&](int32_t i0, int32_t i1, auto nf) {
+    constexpr int NF = decltype(nf)::value;
+    constexpr int U = NBLK >= 4 ? 2 : 4;
+    constexpr int NB = NBLK >= 4 ? 4 : 1;
+    uint64_t m[2][U][NBLK];
+    double f[2][U][NF];
+    for (int32_t c0 = i0; c0 < i1; c0 += 64) {
+      const uint32_t blo = s_lo[min(c0 + lane, kSumTile - 1)], bhi = s_hi[min(c0 + lane, kSumTile - 1)];
+      const int32_t cn = min(64, i1 - c0);
+      auto load = [&](int32_t j, int s) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int32_t l = min(j + u, 63);  // past the end: loaded, not used
+          const uint64_t row = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)bhi, l) << 32) |
+                               (uint32_t)__builtin_amdgcn_readlane((int)blo, l);
+#pragma unroll
+          for (int q = 0; q < NBLK; ++q) m[s][u][q] = mask[row * NBLK + q];
+#pragma unroll
+          for (int k = 0; k < NF; ++k) f[s][u][k] = s_f[min(c0 + l, kSumTile - 1)][k];
+        }
+      };
+      auto add = [&](int s) {
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+          for (int q = 0; q < NBLK; q += NB) add_masked<NF, NB, NP>(acc + q, f[s][u], m[s][u] + q);
+      };
+      auto landed = [&]() {  // wait for the loads of the step before (lgkmcnt 0)
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt(0xc07f);
+        __builtin_amdgcn_sched_barrier(0);
+      };
+      load(0, 0);
+      for (int32_t j = 0; j < cn; j += 2 * U) {  // slots past the run hold zero features
+        landed();
+        load(j + U, 1);
+        __builtin_amdgcn_sched_barrier(0);
+        add(0);
+        landed();
+        load(j + 2 * U, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        add(1);
+      }
+    }
+  };
+
+  int64_t pos = e0;
+  while (pos < e1) {
+    while (P.base[bin + 1] <= pos) ++bin;
+    const int64_t run = min(P.base[bin + 1], e1);
+    const bool dec = bin & 1;
+    double tot[NP];
+#pragma unroll
+    for (int k = 0; k < NP; ++k) tot[k] = 0.0;
+#pragma unroll
+    for (int q = 0; q < NBLK; ++q)
+#pragma unroll
+      for (int k = 0; k < NP; ++k) acc[q][k] = 0.0;
+    for (int64_t t0 = pos; t0 < run; t0 += kSumTile) {
+      const int32_t cnt = uni((int32_t)min((int64_t)kSumTile, run - t0));
+      // ---- stage
+      double f[NP];
+#pragma unroll
+      for (int k = 0; k < NP; ++k) f[k] = 0.0;
+      uint32_t blo = 0, bhi = 0;
+      if (tid < cnt) {
+        const Group<NC == 7> g = ((const Group<NC == 7>*)P.groups)[t0 + tid];
+        blo = g.b;
+        bhi = g.nb >> kNBits;
+        const int64_t row = ((int64_t)bhi << 32) | blo;
+        group_features<NC>(g, (double)(P.nrow[row] & kSizeMask), dec, f);
+        // brings the masks the waves are about to read into the L2
+        uint32_t touch = 0;
+        for (int w = 0; w < P.WS; ++w)
+          touch |= *(const uint32_t*)(P.mask + (w * P.nB + row) * NBLK);
+        asm volatile("" ::"v"(touch));
+#pragma unroll
+        for (int k = 0; k < NP; ++k) tot[k] += f[k];
+      }
+      __syncthreads();  // the previous tile is done with
+      s_lo[tid] = blo;
+      s_hi[tid] = bhi;
+#pragma unroll
+      for (int k = 0; k < NP; ++k) s_f[tid][k] = f[k];
+      __syncthreads();
+      // ---- this wave's part of the tile, a multiple of 2*U groups
+      const int32_t per = ((cnt + WE - 1) / WE + 7) & ~7;
+      const int32_t i0 = min(we * per, cnt), i1 = min(i0 + per, cnt);
+      if (dec) tile(i0, i1, std::integral_constant<int, ND>{});
+      else tile(i0, i1, std::integral_constant<int, NP>{});
+    }
+    // ---- the run's contribution
+#pragma unroll
+    for (int k = 0; k < NP; ++k) {
+      double t = tot[k];
+#pragma unroll
+      for (int d = 32; d >= 1; d >>= 1) t += __shfl_xor(t, d, 64);
+      if (lane == 0) s_tot[wave][k] = t;
+    }
     __syncthreads();
-    if (frg == 0 && fe < fE) {
-      double t = s_fold[tid];
-      for (int g = 1; g < kFoldGroups; ++g) t += s_fold[g * kFoldPer + tid];
-      P.prev_out[fe] = t;
+#pragma unroll
+    for (int k = 0; k < NP; ++k) {
+      tot[k] = s_tot[0][k];
+      for (int w = 1; w < kWaves; ++w) tot[k] += s_tot[w][k];
+      if (we != 0) tot[k] = 0.0;  // the totals once per setting
+    }
+    const int nf = dec ? ND : NP;
+    const double* tm = P.table + (int64_t)(dec ? 2 * NP : 0) * P.ld + ws * NBLK * 64 + lane;
+    const double* tc = tm + (int64_t)nf * P.ld;
+#pragma unroll
+    for (int q = 0; q < NBLK; ++q) {
+      __builtin_amdgcn_sched_barrier(0);  // one block's table rows in registers at a time
+      double r = 0.0;
+#pragma unroll
+      for (int k = 0; k < NP; ++k) {
+        if (k < ND || !dec) {
+          r += tm[(int64_t)k * P.ld + q * 64] * (tot[k] - acc[q][k]);
+          r += tc[(int64_t)k * P.ld + q * 64] * acc[q][k];
+        }
+      }
+      if (WE == 1) P.part[((int64_t)blockIdx.x + bin) * P.ld + (ws * NBLK + q) * 64 + lane] = r;
+      else s_red[wave][q * 64 + lane] = r;
+    }
+    if (WE > 1) {
+      __syncthreads();
+      for (int i = tid; i < P.ld; i += kWG) {
+        const int w = i / (NBLK * 64);
+        double r = 0.0;
+        for (int e = 0; e < WE; ++e) r += s_red[e * P.WS + w][i % (NBLK * 64)];
+        P.part[((int64_t)blockIdx.x + bin) * P.ld + i] = r;
+      }
+    }
+    pos = run;
+    __syncthreads();  // s_tot and s_red are rewritten by the next run
+  }
+}
+
+// k_sweep_sum for a round of at most NV settings, where 64 lanes of settings
+// would stand mostly empty: the lanes take groups, two each at a time, and
+// every lane adds (thetaC - thetaM) . features of its groups under the
+// settings whose bit is set; with thetaM . A that is the same sum.  One wave
+// per chunk (no large ones), no LDS.  Bound by the fp64 rate at 32 settings,
+// by the groups' gathers below: 5.4M groups under 4 settings took 218 us in
+// k_sweep_sum<5, 1>.
+template <int NC, int NV>
+__global__ __launch_bounds__(kWG) void k_sweep_few(const SweepSum P) {
+  constexpr int NP = kPreFeatures<NC>, ND = kDecFeatures;
+  typedef const __attribute__((address_space(4))) double* ScalarPtr;
+  const int lane = threadIdx.x & 63;
+  const int chunk = uni((int32_t)(blockIdx.x * kWaves + (threadIdx.x >> 6)));
+  const int chunks = gridDim.x * kWaves;
+  const SumChunks C(P.base[P.bins], chunks, chunks);
+  const int64_t e0 = C.start(chunk), e1 = C.start(chunk + 1);
+  if (e0 >= e1) return;
+  int bin = bin_of(P.base, P.bins, e0);
+  int64_t pos = e0;
+  while (pos < e1) {
+    while (P.base[bin + 1] <= pos) ++bin;
+    const int64_t run = min(P.base[bin + 1], e1);
+    const bool dec = bin & 1;
+    double acc[NV], tot[NP];
+#pragma unroll
+    for (int v = 0; v < NV; ++v) acc[v] = 0.0;
+#pragma unroll
+    for (int k = 0; k < NP; ++k) tot[k] = 0.0;
+    auto walk = [&](auto nf) {
+      constexpr int NF = decltype(nf)::value;
+      uint64_t diff = (uint64_t)(P.diff + (NF == ND ? 64 * 8 : 0));
+#pragma unroll 1
+      for (int64_t t0 = pos; t0 < run; t0 += 128) {
+        // read anew in every step (held over the steps the table would not fit
+        // the scalar registers)
+        asm volatile("" : "+s"(diff));
+        const ScalarPtr D = (ScalarPtr)diff;
+        double f[2][NP];
+        uint32_t m[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          const int64_t t = t0 + 64 * u + lane;
+          m[u] = 0;
+#pragma unroll
+          for (int k = 0; k < NP; ++k) f[u][k] = 0.0;
+          if (t < run) {
+            const Group<NC == 7> g = ((const Group<NC == 7>*)P.groups)[t];
+            const int64_t row = ((int64_t)(g.nb >> kNBits) << 32) | g.b;
+            m[u] = (uint32_t)P.mask[row];
+            group_features<NC>(g, (double)(P.nrow[row] & kSizeMask), NF == ND, f[u]);
+          }
+#pragma unroll
+          for (int k = 0; k < NF; ++k) tot[k] += f[u][k];
+        }
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+          double d[2] = {0.0, 0.0};
+#pragma unroll
+          for (int k = 0; k < NF; ++k) {
+            const double c = D[v * 8 + k];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) d[u] = fma(c, f[u][k], d[u]);
+          }
+#pragma unroll
+          for (int u = 0; u < 2; ++u) acc[v] += ((m[u] >> v) & 1u) ? d[u] : 0.0;
+        }
+      }
+    };
+    if (dec) walk(std::integral_constant<int, ND>{});
+    else walk(std::integral_constant<int, NP>{});
+    // ---- the run's contribution.  The sums over the lanes halve the settings
+    // a lane holds with every step, until lane l holds setting l / (64 / NV).
+    int d = 32;
+#pragma unroll
+    for (int w = NV / 2; w >= 1; w /= 2, d /= 2) {
+      const bool up = (lane & d) != 0;
+#pragma unroll
+      for (int i = 0; i < w; ++i) {
+        const double give = up ? acc[i] : acc[i + w], keep = up ? acc[i + w] : acc[i];
+        acc[i] = keep + __shfl_xor(give, d, 64);
+      }
+    }
+    double r = acc[0];
+    for (; d >= 1; d /= 2) r += __shfl_xor(r, d, 64);
+    const int v = lane / (64 / NV);
+    const double* tm = P.table + (int64_t)(dec ? 2 * NP : 0) * P.ld + v;
+#pragma unroll
+    for (int k = 0; k < NP; ++k) {
+      double t = tot[k];
+#pragma unroll
+      for (int e = 32; e >= 1; e >>= 1) t += __shfl_xor(t, e, 64);
+      if (k < ND || !dec) r += tm[(int64_t)k * P.ld] * t;
+    }
+    if (lane % (64 / NV) == 0) P.part[((int64_t)chunk + bin) * P.ld + v] = r;
+    pos = run;
+  }
+}
+
+// out[(v0 + s)*T + t] = the contributions of tenant t's two bins under
+// setting s, in a fixed order.  A block takes 64 settings and 8 tenants: its
+// waves read the rows along the settings (each every W-th row of a bin, the
+// rows of all 16 bins at once), the block writes along the tenants.
+// Dynamic LDS: W*8*64 doubles.
+constexpr int kOutTenants = 8;
+__global__ __launch_bounds__(1024) void k_sweep_out(const int64_t* __restrict__ base, int32_t T,
+                                                    int chunks, int big,
+                                                    const double* __restrict__ part, int32_t ld,
+                                                    int32_t n, double* __restrict__ out) {
+  extern __shared__ double s_part[];  // [W][8][64]
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, W = blockDim.x >> 6;
+  const int t0 = blockIdx.x * kOutTenants, s0 = blockIdx.y * 64;
+  const SumChunks C(base[2 * T], chunks, big);
+  // lane j < 16: the chunks of bin 2*t0 + j
+  int32_t i0 = 0, i1 = -1;
+  const int bin = 2 * t0 + lane;
+  if (lane < 2 * kOutTenants && bin < 2 * T) {
+    const int64_t g0 = base[bin], g1 = base[bin + 1];
+    if (g1 > g0) {
+      i0 = (int32_t)C.owner(g0);
+      i1 = (int32_t)C.owner(g1 - 1);
+    }
+  }
+  int rows = lane < 2 * kOutTenants ? i1 - i0 + 1 : 0;  // the most rows of a bin
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) rows = max(rows, __shfl_xor(rows, d, 64));
+  double acc[2 * kOutTenants];
+#pragma unroll
+  for (int j = 0; j < 2 * kOutTenants; ++j) acc[j] = 0.0;
+  for (int k = wave; k < rows; k += W) {
+#pragma unroll
+    for (int j = 0; j < 2 * kOutTenants; ++j) {
+      const int i = __builtin_amdgcn_readlane(i0, j) + k;
+      if (i <= __builtin_amdgcn_readlane(i1, j))
+        acc[j] += part[((int64_t)i + 2 * t0 + j) * ld + s0 + lane];
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < kOutTenants; ++j)
+    s_part[(wave * kOutTenants + j) * 64 + lane] = acc[2 * j] + acc[2 * j + 1];
+  __syncthreads();
+  for (int i = threadIdx.x; i < 64 * kOutTenants; i += blockDim.x) {
+    const int s = i / kOutTenants, j = i % kOutTenants;
+    if (s0 + s < n && t0 + j < T) {
+      double r = s_part[j * 64 + s];
+      for (int w = 1; w < W; ++w) r += s_part[(w * kOutTenants + j) * 64 + s];
+      out[(int64_t)(s0 + s) * T + t0 + j] = r;
     }
   }
 }

@@ -169,6 +169,7 @@ struct Params {
   // them for k_long (count at *long_count = claims[kLongCounter]).
   int64_t* long_list;
   unsigned long long* long_count;
+  int64_t phase_bit;          // added to |B| in bsums row 0 of a prefill batch (0: none)
   int32_t n_tenants;
   int32_t hist_rep;         // MODE_ATTR, HIST_LDS: histogram replicas (1, 2 or 4)
   double S[4];              // shape constants
@@ -243,7 +244,7 @@ __device__ __forceinline__ void batch_model(const Params& P, int64_t bg, int64_t
     if (P.x_batch)
       for (int q = 0; q < 5; ++q) P.x_batch[q * P.nB + bg] = X[q];
     if (P.bsums) {
-      P.bsums[0 * P.nB + bg] = n;
+      P.bsums[0 * P.nB + bg] = n + (prefill ? P.phase_bit : 0);
       P.bsums[1 * P.nB + bg] = (int64_t)Psum;
       P.bsums[2 * P.nB + bg] = (int64_t)Csum;
       P.bsums[3 * P.nB + bg] = (int64_t)Qsum;
@@ -298,7 +299,7 @@ __device__ __forceinline__ void sums_out(const Params& P, int64_t bg, int64_t n,
                                          uint64_t Csum, uint64_t Qsum, uint64_t Rsum,
                                          bool prefill) {
   if (P.bsums) {
-    P.bsums[0 * P.nB + bg] = n;
+    P.bsums[0 * P.nB + bg] = n + (prefill ? P.phase_bit : 0);
     P.bsums[1 * P.nB + bg] = (int64_t)Psum;
     P.bsums[2 * P.nB + bg] = (int64_t)Csum;
     P.bsums[3 * P.nB + bg] = (int64_t)Qsum;

@@ -71,3 +71,104 @@ def test_feature_rows_at_every_alignment(L, tail):
     assert parity.rel_err(xr.cpu().numpy(), rr).max() <= 2.0 ** -23
     assert parity.rel_err(xb.cpu().numpy(), rb).max() <= 1e-12
     assert torch.equal(only_r, xr) and torch.equal(only_b, xb)
+
+
+# ------------------------------------------------------------ what-if sweep
+
+# A tenant's sum is fp64 sums of features with the groups' integer sums
+# rounded to fp32 (2^-24 relative each), times fp64 coefficients: with
+# nonnegative terms within 2^-24 of exact plus fp64 rounding; 2^-23 bounds it.
+SWEEP_RTOL = 2.0 ** -23
+
+
+def check_sweep(L, tr, shapes, co, ext, pairs, tag):
+    import torch
+    dt = L.DeviceTrace.from_host(tr.offsets, tr.p, tr.c, tr.tenant)
+    out = L.attribute_sweep(dt, shapes, co, tr.n_tenants, ext=ext)
+    torch.cuda.synchronize()
+    out = out.cpu().numpy()
+    attr = oracle.attribute_ext if ext else oracle.attribute
+    worst = 0.0
+    for s, v in pairs:
+        ref = attr(tr.offsets, tr.p, tr.c, tr.tenant, None if shapes is None else shapes[s], co[v],
+                   tr.n_tenants, ("tenant_sums",))["tenant_sums"]
+        assert np.array_equal(out[s, v][ref == 0], ref[ref == 0]), (tag, s, v)
+        worst = max(worst, float(parity.rel_err(out[s, v], ref).max()))
+    say(f"[sweep] {tag}: max rel err {worst:.2e}")
+    assert worst <= SWEEP_RTOL, (tag, worst)
+    return out
+
+
+def sweep_sets(n, ext, seed=300):
+    rng = np.random.default_rng(seed)
+    base = tracegen.ext_coeffs(seed) if ext else tracegen.base_coeffs(seed)
+    return (base[None, :] * rng.uniform(0.7, 1.4, (n, len(base)))).astype(np.float32)
+
+
+@pytest.mark.parametrize("ext", [False, True])
+@pytest.mark.parametrize("n_shapes,n", [(1, 1), (1, 63), (1, 64), (1, 65), (2, 64), (3, 43), (1, 256),
+                                        (1, 257), (2, 256), (1, 513), (4, 256), (3, 342), (1, 1025)])
+def test_sweep_settings(L, n_shapes, n, ext):
+    """Setting counts around the 64-setting blocks, the blocks per wave (1, 2,
+    4, 8), the waves side by side, the 1024-setting rounds, and more
+    coefficient vectors than a round holds: the first and last settings of
+    blocks and rounds against the oracle."""
+    rng = np.random.default_rng(n)
+    tr = fill(rng, rng.integers(0, 200, 120), n_tenants=33, p_empty=0.1)
+    shapes = [tracegen.SHAPES[k] for k in sorted(tracegen.SHAPES)][:n_shapes]
+    co = sweep_sets(n, ext)
+    last = n_shapes * n - 1
+    at = sorted({min(max(v, 0), last) for e in (0, 64, 512, 1024, last + 1) for v in (e - 1, e, e + 1)})
+    check_sweep(L, tr, shapes, co, ext, [(v // n, v % n) for v in at], f"{n_shapes}x{n} ext={ext}")
+
+
+@pytest.mark.parametrize("ext", [False, True])
+@pytest.mark.parametrize("case", ["singles", "few-per-batch", "one-tenant", "hot-tenant", "bins-4096"])
+def test_sweep_group_shapes(L, case, ext):
+    """Rounds of 64 settings where the masks have no room for more (batches of
+    one request), bins of no, one and many groups, chunks that end inside and
+    on a bin's end, and both phases of every tenant."""
+    rng = np.random.default_rng(sum(map(ord, case)))
+    if case == "singles":
+        tr = fill(rng, np.ones(5000, np.int64), n_tenants=9, p_empty=0.3)
+    elif case == "few-per-batch":
+        tr = fill(rng, rng.integers(0, 5, 4000), n_tenants=700)
+    elif case == "one-tenant":
+        tr = fill(rng, rng.integers(1, 40, 9000), n_tenants=1)
+    elif case == "hot-tenant":
+        tr = fill(rng, rng.integers(1, 300, 700), n_tenants=200)
+        tr.tenant[rng.random(tr.n_requests) < 0.9] = 77
+    else:
+        tr = fill(rng, rng.integers(1, 900, 60), n_tenants=4096)
+    shapes = [tracegen.SHAPES["qwen2.5-14b"], tracegen.SHAPES["70b-like"]]
+    co = sweep_sets(70, ext, 400)
+    check_sweep(L, tr, shapes, co, ext, [(0, 0), (0, 63), (0, 64), (1, 0), (1, 57), (1, 58), (1, 69)],
+                f"{case} ext={ext}")
+
+
+def test_sweep_under_capture(L):
+    """The settings are host arrays: a captured sweep keeps their values, and
+    replays after other work give the same sums."""
+    import torch
+    rng = np.random.default_rng(8)
+    tr = fill(rng, rng.integers(0, 200, 300), n_tenants=50)
+    dt = L.DeviceTrace.from_host(tr.offsets, tr.p, tr.c, tr.tenant)
+    shapes = [tracegen.SHAPES["llama3.1-8b"]]
+    co = sweep_sets(100, False)
+    ws = L.sweep_workspace(tr.n_batches, tr.n_requests, 50)
+    want = L.attribute_sweep(dt, shapes, co, 50).cpu()
+    out = torch.empty((1, 100, 50), dtype=torch.float64, device="cuda")
+    L.llmv_attribute_sweep(dt, shapes, co, 50, out, ws)  # loads the kernels
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        L.llmv_attribute_sweep(dt, shapes, co, 50, out, ws)
+    co[:] = 0.0
+    for _ in range(3):
+        out.fill_(-1.0)
+        ws.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        np.testing.assert_allclose(out.cpu().numpy(), want.numpy(), rtol=1e-12)
+        L.attribute(dt, shapes[0], tracegen.base_coeffs(3), 50)
+        torch.cuda.synchronize()
