@@ -7,6 +7,7 @@
 #include <cstdio>
 #include <cstring>
 #include <mutex>
+#include <type_traits>
 
 #include "host.hpp"
 #include "groups.hpp"
@@ -53,6 +54,7 @@ int scratch_address(void** out) {
 // no more than one workgroup per kWaves (narrow) wave tiles of requests, at
 // most kMaxGrid.
 int64_t grid_max_for(int64_t n) {
+  if (n <= kShortMost) return kShortGrid;
   const int64_t per = (int64_t)kCapNarrow * kWaves;
   const int64_t by_work = (n + per - 1) / per;
   return by_work < 1 ? 1 : (by_work > kMaxGrid ? kMaxGrid : by_work);
@@ -91,7 +93,7 @@ int hist_replicas(int32_t T) {
 }
 
 struct Layout {
-  size_t wg_first, claims, partials, flag, big_list, big_seg, long_list, total;
+  size_t wg_first, claims, partials, flag, big_list, big_seg, long_list, short_long, total;
 };
 
 // Chunks for `workers` wave workers over n requests, for wave tiles of `cap`
@@ -156,6 +158,8 @@ Layout layout(int64_t n, int32_t T) {
   o += align_up(((size_t)(n / kBigSeg) + 2 * n_list) * sizeof(uint64_t));
   L.long_list = o;  // batches larger than a wave tile (each more than kCapNarrow - 3 requests)
   o += align_up((size_t)(n / (kCapNarrow - 3) + 1) * sizeof(int64_t));
+  L.short_long = o;  // short trace: the waves' lists and their counts
+  if (n <= kShortMost) o += align_up((size_t)kShortGrid * kWaves * (kShortLong + 1) * sizeof(int64_t));
   L.total = o;
   return L;
 }
@@ -287,6 +291,40 @@ template <> struct TilePick<ExtModel> {
   }
 };
 
+// The two kernels of a short trace (attribution, no tenant cache).
+template <int MODE, int HIST, bool SHARE, typename VT>
+int launch_short(const Params& P, const VT& V, int grid, size_t dyn, hipStream_t st) {
+  if (g_ev_before) HIP_TRY(hipEventRecord(g_ev_before, st), "hipEventRecord");
+  hipLaunchKernelGGL((k_tiles<MODE, HIST, SHARE, kVecShort>), dim3(grid), dim3(kWG), dyn, st, P, V);
+  HIP_TRY(hipGetLastError(), "k_tiles launch");
+  if (g_ev_after) HIP_TRY(hipEventRecord(g_ev_after, st), "hipEventRecord");
+  hipLaunchKernelGGL((k_finish<MODE, HIST, SHARE>), dim3(grid), dim3(kWG), dyn, st, P, V);
+  HIP_TRY(hipGetLastError(), "k_finish launch");
+  return LLMV_OK;
+}
+
+template <int MODE, typename VT>
+int run_short(const llmv_trace* tr, Params& P, const VT& V, const Layout& L, bool want_share,
+              size_t dyn, void* ws, hipStream_t st) {
+  const int64_t n = tr->n_requests;
+  const int grid = (int)((n + kCapShort * kWaves - 1) / (kCapShort * kWaves));
+  P.short_run = 1;
+  P.chunk_len = (n + (int64_t)grid * kWaves - 1) / ((int64_t)grid * kWaves);
+  // a chunk of at most kCapShort requests starts at most two batches of more
+  // than kCapShort - 4
+  static_assert(kShortLong >= 2, "a wave's long batches");
+  P.n_chunks = (int64_t)grid * kWaves;
+  P.n_static = P.n_chunks;
+  P.partials = P.n_tenants ? (double*)((char*)ws + L.partials) : nullptr;
+  P.long_list = (int64_t*)((char*)ws + L.short_long);
+  P.long_count = (unsigned long long*)(P.long_list + (int64_t)kShortGrid * kWaves * kShortLong);
+  if (P.n_tenants)
+    return want_share ? launch_short<MODE, HIST_LDS, true>(P, V, grid, dyn, st)
+                      : launch_short<MODE, HIST_LDS, false>(P, V, grid, dyn, st);
+  return want_share ? launch_short<MODE, HIST_NONE, true>(P, V, grid, dyn, st)
+                    : launch_short<MODE, HIST_NONE, false>(P, V, grid, dyn, st);
+}
+
 // The long-batch kernel matching a tile kernel.
 template <typename VT> struct LongPick;
 template <> struct LongPick<NoVars> {
@@ -361,6 +399,13 @@ int run_tiles(int mode, const llmv_trace* tr, Params& P, const VT& V, int32_t T,
   const int64_t cap = tile_cap(mode, hist);
   // a batch larger than a tile needs more than cap - 4 requests
   const bool longs = tr->n_requests > cap - 4;
+  if ((mode == MODE_ATTR || mode == MODE_EXT) && hist != HIST_GLOBAL && longs &&
+      tr->n_requests <= kShortMost) {
+    if constexpr (std::is_same<VT, ExtModel>::value)
+      return run_short<MODE_EXT>(tr, P, V, L, want_share, dyn, ws, stream);
+    else
+      return run_short<MODE_ATTR>(tr, P, V, L, want_share, dyn, ws, stream);
+  }
   if (tr->n_requests <= small_n(cap) && hist != HIST_GLOBAL) {
     // A small trace (one scheduler step, say) in one launch: one workgroup,
     // its waves split the batches by count (no chunk table), and the

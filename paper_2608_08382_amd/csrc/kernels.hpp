@@ -42,6 +42,7 @@ constexpr int kWaves = kWG / 64;             // wave64
 // the two: kVecOf below); a wave tile holds 64 times as many.
 constexpr int kVecNarrow = 24;
 constexpr int kVecWide = 28;
+constexpr int kVecShort = 8;                 // of a short trace (kShortMost)
 constexpr int kCapNarrow = 64 * kVecNarrow;  // request slots per narrow wave tile
 constexpr int kHistLdsMax = 4096;                // tenants held in an LDS histogram
 constexpr int kMaxGrid = 1024;                   // persistent workgroups, upper bound (256 CUs x 4)
@@ -128,6 +129,22 @@ __host__ __device__ constexpr int64_t tile_cap(int mode, int hist) {
   return 64 * (wide_tile(mode, hist) ? kVecWide : kVecNarrow);
 }
 
+// A short trace: attribution of up to kShortMost requests (with an LDS tenant
+// histogram or no tenant sums) runs on 512-slot tiles, one chunk per wave and
+// about a tile per chunk, in two launches: k_tiles, whose waves find their
+// chunks by searching the offsets, and k_finish, which adds up the tenant
+// partials and takes the batches larger than a tile, which every wave of
+// k_tiles listed for itself.  Nothing is claimed, counted across workgroups or
+// read from a chunk table, so nothing has to be cleared first.  The time of
+// such a trace is that of its launches and of one wave's serial chain, not
+// of its bytes: a call over 1000 batches of 16.6k requests takes 19 us; as
+// 1792-slot tiles on 12 waves in four launches it took 26.  The bound is where batches begin to be worth
+// spreading over workgroups (kListMin).
+constexpr int64_t kCapShort = 64 * kVecShort;
+constexpr int64_t kShortMost = 64 * 64 * kVecWide;
+constexpr int kShortGrid = (int)((kShortMost + kCapShort * kWaves - 1) / (kCapShort * kWaves));
+constexpr int kShortLong = 4;  // long batches of a wave's chunk, at most (run_short)
+
 // A batch listed for the segment kernels: its index and exact sums (sum p,
 // sum c, sum p^2, count of c == 0), accumulated by k_big_sums.
 struct BigEntry {
@@ -146,6 +163,8 @@ struct Params {
   uint64_t claim_base;      // counter value when this launch starts
   int64_t n_chunks;
   int64_t n_static;         // chunks taken statically, round-robin (>= the wave workers)
+  int32_t short_run;        // a short trace: chunk w starts at request w*chunk_len
+  int64_t chunk_len;
   int32_t split_by_count;   // one workgroup, no chunk table: wave w takes batches
                             // [w*nB/4, (w+1)*nB/4) (small traces, one launch)
   float* latency;           // [nB] or null
@@ -167,6 +186,7 @@ struct Params {
   uint64_t* big_seg;          // segments: (list index << 32) | segment within the batch
   // The other batches larger than a wave tile, listed by the wave that meets
   // them for k_long (count at *long_count = claims[kLongCounter]).
+  // Short trace: kShortLong entries per wave, the waves' counts at long_count.
   int64_t* long_list;
   unsigned long long* long_count;
   int64_t phase_bit;          // added to |B| in bsums row 0 of a prefill batch (0: none)
@@ -535,6 +555,23 @@ __device__ __forceinline__ uint32_t wave_incl_scan_u32(uint32_t x) {
   return x;
 }
 
+// The first batch starting at or after request x (nB if none), by the whole
+// wave: every step reads 64 offsets of the range left.
+__device__ __forceinline__ int64_t first_at(const int64_t* __restrict__ off, int64_t nB, int64_t x) {
+  const int lane = threadIdx.x & 63;
+  int64_t lo = 0, hi = nB;  // batches below lo start before x; hi starts at or after it, or is nB
+  while (lo < hi) {
+    const int64_t step = (hi - lo + 63) / 64;
+    const int64_t i = lo + step * lane;
+    const uint64_t ge = __ballot(i >= hi || off[i] >= x);
+    const int k = ge ? __builtin_ctzll(ge) : 64;  // probes below lane k start before x
+    if (k == 0) return lo;
+    hi = min(hi, lo + step * k);
+    lo = lo + step * (k - 1) + 1;
+  }
+  return lo;
+}
+
 // Loads slots x .. x+kVec-1 (x a multiple of 4, x >= 0) of p, c (and
 // tenant); slots at or past N read as 0.
 template <int VEC, bool TENANT>
@@ -698,11 +735,10 @@ __device__ __forceinline__ void load_round(const Params& P, int64_t o, int64_t m
 // once, as in a tile.  A longer one keeps its first round in registers and
 // streams the others twice: for the exact sums, then for the per-request
 // outputs.  wk, wk4: the wave's LDS words for the batch constants.
-template <int MODE, int HIST, bool SHARE>
+template <int MODE, int HIST, bool SHARE, int VEC>
 __device__ __forceinline__ void long_batch(const Params& P, const typename VarsOf<MODE>::type& V, double* wk,
                            double* wk4, float* stage, int64_t bg, int64_t rs, int64_t re,
                            double* s_hist) {
-  constexpr int VEC = kVecOf<MODE, HIST>;
   LLMV_TILE_CONSTANTS(VEC);
   constexpr bool OUT = kPerRequest<MODE, HIST, SHARE>;
   constexpr bool TEN = OUT && HIST != HIST_NONE;
@@ -911,11 +947,11 @@ __device__ __forceinline__ void list_run(const Params& P, int64_t b, int64_t wv,
 // tenant histogram (HIST_LDS) holds hist_rep replicas of n_tenants entries:
 // lane l adds into replica l % hist_rep, so that lanes of one atomic that
 // share a frequent tenant spread over hist_rep entries.
-template <int MODE, int HIST, bool SHARE>
+template <int MODE, int HIST, bool SHARE, int VEC = kVecOf<MODE, HIST>>
 __global__ __launch_bounds__(kWG) void k_tiles(const Params P,
                                                const typename VarsOf<MODE>::type V) {
-  constexpr int VEC = kVecOf<MODE, HIST>;
   LLMV_TILE_CONSTANTS(VEC);
+  constexpr bool SHORT = VEC == kVecShort;  // a short trace (P.short_run)
   extern __shared__ double s_hist[];  // [hist_rep][n_tenants] when HIST_LDS
   __shared__ WaveLds<VEC> s_wave[kWaves];
   constexpr bool STAGE = kStaged<MODE, SHARE>;
@@ -943,7 +979,11 @@ __global__ __launch_bounds__(kWG) void k_tiles(const Params P,
     for (int u = tid; u < n_hist; u += kWG) s_hist[u] = 0.0;
   if (HIST == HIST_GLOBAL) cache_init(s_hist);
   // one workgroup, no k_partition: the count of listed batches starts here
-  if (P.split_by_count && tid == 0) atomicExch(P.long_count, 0ull);
+  if (!SHORT && P.split_by_count && tid == 0) atomicExch(P.long_count, 0ull);
+  // short trace: k_finish adds into the output where there are long batches
+  if (SHORT && HIST == HIST_LDS)
+    for (int u = blockIdx.x * kWG + tid; u < P.n_tenants; u += gridDim.x * kWG)
+      P.tenant_sums[u] = 0.0;
   // this lane's replica of the histogram
   double* s_hist_lane = s_hist;
   if (HIST == HIST_LDS) s_hist_lane = s_hist + (lane & (P.hist_rep - 1)) * P.n_tenants;
@@ -956,8 +996,9 @@ __global__ __launch_bounds__(kWG) void k_tiles(const Params P,
   // claim is issued for the last static chunk and every claimed chunk, so a
   // launch takes W + n_chunks - n_static claims).
   const int64_t workers = (int64_t)gridDim.x * kWaves;
-  const bool dyn = P.n_chunks > P.n_static;
+  const bool dyn = !SHORT && P.n_chunks > P.n_static;
   auto first_batch = [&](int64_t ch) {
+    if constexpr (SHORT) return ch < workers ? first_at(P.off, P.nB, ch * P.chunk_len) : P.nB;
     return P.split_by_count ? P.nB * ch / workers : uni(P.wg_first[ch]);
   };
   // offsets window: lane j holds offsets[x0 + j] for j <= min(kTileBatches, x1 - x0)
@@ -983,10 +1024,16 @@ __global__ __launch_bounds__(kWG) void k_tiles(const Params P,
   // (free between tiles) and flushed to the long list with one atomic
   int64_t* lbuf = (int64_t*)&W.k[0][0];
   int32_t n_long = 0;
+  uint64_t listed = 0;  // short trace: this wave's long batches so far
   auto flush_long = [&]() {
     unsigned long long at = 0;
-    if (lane == 0) at = atomicAdd(P.long_count, (unsigned long long)n_long);
-    at = readlane_u64(at, 0);
+    if constexpr (SHORT) {
+      at = ((uint64_t)blockIdx.x * kWaves + (tid >> 6)) * kShortLong + listed;
+      listed += n_long;
+    } else {
+      if (lane == 0) at = atomicAdd(P.long_count, (unsigned long long)n_long);
+      at = readlane_u64(at, 0);
+    }
     wave_lds_sync();
     for (int32_t i = lane; i < n_long; i += 64) P.long_list[at + i] = lbuf[i];
     wave_lds_sync();
@@ -1262,6 +1309,7 @@ __global__ __launch_bounds__(kWG) void k_tiles(const Params P,
     claim = claim_next(chunk);
   }
   if (n_long) flush_long();
+  if (SHORT && lane == 0) P.long_count[(int64_t)blockIdx.x * kWaves + (tid >> 6)] = listed;
 
   if (HIST == HIST_LDS) {
     // fold the replicas in a fixed order
@@ -1443,10 +1491,9 @@ __global__ __launch_bounds__(kBigWG) void k_big_sums(const Params P) {
 // HIST_GLOBAL: its tenant cache is flushed into the output.
 // Two workgroups per compute unit: a batch of two tiles held whole fits in
 // 256 VGPRs.
-template <int MODE, int HIST, bool SHARE>
+template <int MODE, int HIST, bool SHARE, int VEC = kVecOf<MODE, HIST>>
 __global__ __launch_bounds__(kWG, 2) void k_long(const Params P, const typename VarsOf<MODE>::type V,
                                               int64_t rows) {
-  constexpr int VEC = kVecOf<MODE, HIST>;
   LLMV_TILE_CONSTANTS(VEC);
   constexpr bool STAGE = kStaged<MODE, SHARE>;
   constexpr bool TEN = HIST != HIST_NONE;
@@ -1474,7 +1521,7 @@ __global__ __launch_bounds__(kWG, 2) void k_long(const Params P, const typename 
        k += (uint64_t)gridDim.x * kWaves) {
     const int64_t b = uni(P.long_list[k]);
     const int64_t rs = uni(P.off[b]), re = uni(P.off[b + 1]);
-    long_batch<MODE, HIST, SHARE>(P, V, s_k[wave], &s_k4[wave], stage, b, rs, re, s_hist_lane);
+    long_batch<MODE, HIST, SHARE, VEC>(P, V, s_k[wave], &s_k4[wave], stage, b, rs, re, s_hist_lane);
   }
 
   if constexpr (MODE == MODE_ATTR) {
@@ -1559,6 +1606,71 @@ __global__ __launch_bounds__(kWG, 2) void k_long(const Params P, const typename 
   } else if (HIST == HIST_GLOBAL) {
     __syncthreads();
     cache_flush(s_hist, P.tenant_sums);
+  }
+}
+
+// The end of a short trace (kShortMost), after k_tiles on the same grid.
+// Workgroup w adds up its tenants' columns of the partials (64 tenants at a
+// time, its waves every kWaves-th row), then its waves walk the long batches that
+// the same waves of k_tiles listed, and the workgroup's histogram of those is
+// added to the output (cleared by k_tiles) with fp64 atomics, as then are the
+// column sums.  Bound by its launch and two or three round trips to memory.
+template <int MODE, int HIST, bool SHARE>
+__global__ __launch_bounds__(kWG, 2) void k_finish(const Params P,
+                                                  const typename VarsOf<MODE>::type V) {
+  constexpr int VEC = kVecShort;
+  LLMV_TILE_CONSTANTS(VEC);
+  constexpr bool STAGE = kStaged<MODE, SHARE>;
+  extern __shared__ double s_hist[];  // HIST_LDS: [hist_rep][n_tenants]
+  __shared__ double s_k[kWaves][4];
+  __shared__ double s_k4[kWaves];
+  __shared__ float s_stage[STAGE ? kWaves * 64 * kStagePitch : 1];
+  __shared__ double s_col[kWaves][64];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int n_waves = gridDim.x * kWaves;
+  bool mine = false;
+  for (int w = tid; w < n_waves; w += kWG) mine |= P.long_count[w] != 0;
+  const bool any = __syncthreads_or(mine);  // some batch is longer than a tile
+  const int32_t T = P.n_tenants, rows = gridDim.x;
+  if (HIST == HIST_LDS) {
+    for (int u0 = blockIdx.x * 64; u0 < T; u0 += rows * 64) {
+      double acc = 0.0;
+      if (u0 + lane < T) {
+#pragma unroll 8
+        for (int r = wave; r < rows; r += kWaves) acc += P.partials[(int64_t)r * T + u0 + lane];
+      }
+      s_col[wave][lane] = acc;
+      __syncthreads();
+      if (wave == 0 && u0 + lane < T) {
+        double t = s_col[0][lane];
+        for (int w = 1; w < kWaves; ++w) t += s_col[w][lane];
+        if (any) unsafeAtomicAdd(P.tenant_sums + u0 + lane, t);
+        else P.tenant_sums[u0 + lane] = t;
+      }
+      __syncthreads();
+    }
+  }
+  const int64_t w = (int64_t)blockIdx.x * kWaves + wave;
+  const int n_long = (int)uni((int64_t)P.long_count[w]);
+  if (__syncthreads_or(n_long) == 0) return;  // none in this workgroup
+  if (HIST == HIST_LDS)
+    for (int u = tid; u < P.hist_rep * T; u += kWG) s_hist[u] = 0.0;
+  double* s_hist_lane = s_hist;
+  if (HIST == HIST_LDS) s_hist_lane = s_hist + (lane & (P.hist_rep - 1)) * T;
+  __syncthreads();
+  float* stage = s_stage + (STAGE ? wave * 64 * kStagePitch : 0);
+  for (int k = 0; k < n_long; ++k) {
+    const int64_t b = uni(P.long_list[w * kShortLong + k]);
+    const int64_t rs = uni(P.off[b]), re = uni(P.off[b + 1]);
+    long_batch<MODE, HIST, SHARE, VEC>(P, V, s_k[wave], &s_k4[wave], stage, b, rs, re, s_hist_lane);
+  }
+  if (HIST == HIST_LDS) {
+    __syncthreads();
+    for (int u = tid; u < T; u += kWG) {
+      double acc = s_hist[u];
+      for (int r = 1; r < P.hist_rep; ++r) acc += s_hist[r * T + u];
+      if (acc != 0.0) unsafeAtomicAdd(P.tenant_sums + u, acc);
+    }
   }
 }
 

@@ -172,3 +172,52 @@ def test_sweep_under_capture(L):
         np.testing.assert_allclose(out.cpu().numpy(), want.numpy(), rtol=1e-12)
         L.attribute(dt, shapes[0], tracegen.base_coeffs(3), 50)
         torch.cuda.synchronize()
+
+
+# ------------------------------------------------------------ short traces
+
+
+def sized(rng, N, lo, hi, extra=()):
+    """Batch sizes from lo..hi (and the extra ones) adding up to N."""
+    sizes = list(extra)
+    while sum(sizes) < N:
+        sizes.append(int(min(rng.integers(lo, hi + 1), N - sum(sizes))))
+    rng.shuffle(sizes)
+    assert sum(sizes) == N
+    return sizes
+
+
+@pytest.mark.parametrize("ext", [False, True])
+@pytest.mark.parametrize("N,lo,hi,extra,T", [
+    (1789, 1, 40, (0, 0), 1),                        # the first of the two-launch traces
+    (2048, 0, 9, (508, 509, 512), 7),                # one workgroup; around a 512-slot tile
+    (2049, 512, 513, (), 16),                        # every batch about a tile
+    (4097, 0, 3, (), 4096),                          # more batches than offsets in a window
+    (9000, 505, 520, (0, 1, 2), 300),                # tiles and long batches next to each other
+    (14337, 1, 2000, (), 64),
+    (40001, 0, 60, (30000,), 1024),                  # one batch over most of the chunks
+    (114688, 0, 300, (0, 5000, 1025, 1024), 1000),   # the longest short trace
+    (114689, 0, 300, (0, 5000, 1025, 1024), 1000),   # the next path
+])
+def test_short_trace(L, N, lo, hi, extra, T, ext):
+    import torch
+    rng = np.random.default_rng(N + T)
+    sizes = sized(rng, N, lo, hi, extra)
+    tr = fill(rng, [0, 0] + sizes + [0] * 70, n_tenants=T)
+    shape = tracegen.SHAPES["llama3.1-8b"]
+    co = tracegen.ext_coeffs(5) if ext else tracegen.base_coeffs(5)
+    say(f"[short] N={tr.n_requests} nB={tr.n_batches} T={T} ext={ext}")
+    dt = L.DeviceTrace.from_host(tr.offsets, tr.p, tr.c, tr.tenant)
+    run, orc = ((L.attribute_ext, oracle.attribute_ext) if ext else (L.attribute, oracle.attribute))
+    ref = orc(tr.offsets, tr.p, tr.c, tr.tenant, shape, co, T)
+    for _ in range(2):  # the second call finds the first one's scratch
+        g = {k: v.cpu().numpy() for k, v in run(dt, shape, co, T).items()}
+        parity.compare(ref, tr.offsets, g["latency"], g["regime"], g["share"], g["tenant_sums"])
+    for outs in (("latency", "tenant_sums"), ("share",), ("regime",)):
+        h = run(dt, shape, co, T, outs)
+        torch.cuda.synchronize()
+        for k in outs:
+            if k == "tenant_sums":
+                np.testing.assert_allclose(h[k].cpu().numpy(), g[k], rtol=1e-12)
+            else:
+                assert np.array_equal(h[k].cpu().numpy(), g[k]), (outs, k)
