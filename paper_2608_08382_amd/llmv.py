@@ -8,9 +8,11 @@ library is missing, loading fails with an error.
 from __future__ import annotations
 
 import ctypes
+import operator
 import os
 import threading
 
+import numpy as np
 import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
@@ -58,6 +60,8 @@ _lib = None
 def load(path: str = LIB_PATH):
     """Loads libllmv; raises if it has not been built."""
     global _lib
+    if _lib is not None:
+        return _lib
     with _lock:
         if _lib is None:
             if not os.path.exists(path):
@@ -113,27 +117,54 @@ def _check(rc: int, func: str):
         raise LlmvError(rc, func, load().llmv_last_error().decode())
 
 
+# The arguments of a call are marshalled in every call (nothing is kept of
+# them).  For a step of a few hundred requests this is most of the call's time,
+# so the common forms take the short way: addresses as plain integers (the
+# functions' argtypes convert them), an fp32 array's bytes, the raw stream
+# without a Stream object (a step of 256 requests takes 6.6 us a call, 11.4 before).
+
 def _ptr(t):
+    """The address of a contiguous tensor; None for None and an empty one."""
     if t is None:
         return None
     if not isinstance(t, torch.Tensor):
         raise TypeError("expected a torch tensor")
-    if t.numel() and not t.is_contiguous():
+    if not t.numel():
+        return None
+    if not t.is_contiguous():
         raise ValueError("tensors must be contiguous")
-    return ctypes.c_void_p(t.data_ptr()) if t.numel() else None
+    return t.data_ptr()
+
+
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
 def _stream(stream):
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
+
+
+def _floats(values, k):
+    """k host fp32 numbers for one call."""
+    if type(values) is np.ndarray and values.dtype == np.float32 and values.shape == (k,):
+        return values.tobytes()
+    return (ctypes.c_float * k)(*[float(v) for v in values])
+
+
+_shape_fields = operator.itemgetter(*[f[0] for f in llmv_shape._fields_])
 
 
 def make_shape(shape) -> llmv_shape | None:
     """shape: None, a dict with the nine field names, or llmv_shape."""
     if shape is None or isinstance(shape, llmv_shape):
         return shape
-    return llmv_shape(*[int(shape[f[0]]) for f in llmv_shape._fields_])
+    try:
+        return llmv_shape(*_shape_fields(shape))
+    except TypeError:  # numbers other than int
+        return llmv_shape(*[int(shape[f[0]]) for f in llmv_shape._fields_])
 
 
 def _shape_ref(sh):
@@ -185,7 +216,7 @@ def llmv_sweep_workspace_size_ext(n_batches: int, n_requests: int, n_tenants: in
 
 def llmv_attribute(trace: DeviceTrace, shape, coeffs, latency=None, regime=None, share=None,
                    n_tenants: int = 0, tenant_sums=None, ws=None, stream=None):
-    co = (ctypes.c_float * 20)(*[float(v) for v in coeffs])
+    co = _floats(coeffs, 20)
     sh = make_shape(shape)
     tr = trace.struct(with_tenant=tenant_sums is not None)
     nbytes = 0 if ws is None else ws.numel() * ws.element_size()
@@ -197,7 +228,7 @@ def llmv_attribute(trace: DeviceTrace, shape, coeffs, latency=None, regime=None,
 def llmv_attribute_noalloc(trace: DeviceTrace, shape, coeffs, latency=None, regime=None,
                            share=None, n_tenants: int = 0, tenant_sums=None, stream=None):
     """llmv_attribute without a workspace (the library's static scratch)."""
-    co = (ctypes.c_float * 20)(*[float(v) for v in coeffs])
+    co = _floats(coeffs, 20)
     sh = make_shape(shape)
     tr = trace.struct(with_tenant=tenant_sums is not None)
     _check(load().llmv_attribute_noalloc(ctypes.byref(tr), _shape_ref(sh), co, _ptr(latency),
@@ -211,7 +242,6 @@ def llmv_attribute_host(offsets, p, c, tenant, shape, coeffs, n_tenants: int = 0
     """llmv_attribute_host on host (numpy) arrays: returns the requested
     outputs as numpy arrays.  The arrays are passed to the library as they
     are (contiguous, converted to int64 / int32 first)."""
-    import numpy as np
     off = np.ascontiguousarray(offsets, dtype=np.int64)
     pp = np.ascontiguousarray(p, dtype=np.int32)
     cc = np.ascontiguousarray(c, dtype=np.int32)
@@ -220,7 +250,7 @@ def llmv_attribute_host(offsets, p, c, tenant, shape, coeffs, n_tenants: int = 0
     nB, N = len(off) - 1, len(pp)
 
     def hp(a):
-        return None if a is None or a.size == 0 else ctypes.c_void_p(a.ctypes.data)
+        return None if a is None or a.size == 0 else a.__array_interface__["data"][0]
 
     tr = llmv_trace(nB, N, hp(off), hp(pp), hp(cc), hp(tt))
     out = {}
@@ -232,7 +262,7 @@ def llmv_attribute_host(offsets, p, c, tenant, shape, coeffs, n_tenants: int = 0
         out["share"] = np.zeros(N, np.float32)
     if want_t:
         out["tenant_sums"] = np.zeros(int(n_tenants), np.float64)
-    co = (ctypes.c_float * 20)(*[float(v) for v in coeffs])
+    co = _floats(coeffs, 20)
     sh = make_shape(shape)
     _check(load().llmv_attribute_host(ctypes.byref(tr), _shape_ref(sh), co,
                                       hp(out.get("latency")), hp(out.get("regime")),
@@ -246,7 +276,6 @@ def llmv_attribute_sweep(trace: DeviceTrace, shapes, coeffs, n_tenants: int, out
     """shapes: list of shape dicts (or [None] for the unit shape); coeffs:
     array-like [n_coeffs, 20] ([n_coeffs, 28] with ext: llmv_attribute_sweep_ext);
     out: device fp64 [n_shapes, n_coeffs, n_tenants]."""
-    import numpy as np
     co = np.ascontiguousarray(coeffs, dtype=np.float32).reshape(-1, 28 if ext else 20)
     if shapes == [None] or shapes is None:
         arr, n_sh = None, 1
@@ -290,7 +319,7 @@ def llmv_admit(sums, phase, n_batches: int, shape, coeffs, cand_batch, cand_p, c
     With ext the extended model (llmv_admit_ext): sums [5, n_batches], 28
     coefficients."""
     k = 28 if ext else 20
-    co = (ctypes.c_float * k)(*[float(v) for v in coeffs])
+    co = _floats(coeffs, k)
     sh = make_shape(shape)
     m = int(cand_p.numel())
     fn, name = (load().llmv_admit_ext, "llmv_admit_ext") if ext else (load().llmv_admit,
@@ -319,10 +348,11 @@ def llmv_attribute_ext(trace: DeviceTrace, shape, coeffs, latency=None, regime=N
                        n_tenants: int = 0, tenant_sums=None, ws=None, stream=None):
     """llmv_attribute under the extended model: coeffs holds 28 numbers,
     index (phase*2 + segment)*7 + k, k = (beta, a1, ..., a6)."""
-    vals = [float(v) for v in coeffs]
-    if len(vals) != 28:
+    if type(coeffs) is not np.ndarray:
+        coeffs = [float(v) for v in coeffs]
+    if len(coeffs) != 28:
         raise ValueError("the extended model takes 28 coefficients")
-    co = (ctypes.c_float * 28)(*vals)
+    co = _floats(coeffs, 28)
     sh = make_shape(shape)
     if ws is None:
         ws = workspace(trace.n_batches, trace.n_requests, n_tenants, trace.p.device)
@@ -362,7 +392,7 @@ def llmv_fit_metrics(sums, phase, shape, coeffs, y, out, rel_err=None, ws=None, 
     extended model (llmv_fit_metrics_ext, 28 coefficients)."""
     n = int(phase.numel())
     k = 28 if ext else 20
-    co = (ctypes.c_float * k)(*[float(v) for v in coeffs])
+    co = _floats(coeffs, k)
     sh = make_shape(shape)
     if ws is None:
         ws = fit_workspace(n, out.device)
@@ -458,7 +488,6 @@ def attribute_sweep(trace: DeviceTrace, shapes, coeffs, n_tenants: int, ws=None,
                     ext: bool = False):
     """Allocates out [n_shapes, n_coeffs, n_tenants] and runs the sweep (under
     the extended model with ext, coeffs [n_coeffs, 28])."""
-    import numpy as np
     n_sh = 1 if shapes is None else len(shapes)
     n_co = int(np.asarray(coeffs).reshape(-1, 28 if ext else 20).shape[0])
     out = torch.empty((n_sh, n_co, n_tenants), dtype=torch.float64, device=trace.p.device)
