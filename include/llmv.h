@@ -104,7 +104,10 @@ typedef struct {
 int llmv_shape_constants(const llmv_shape *shape, double S[4]);
 
 /* Bytes of device workspace every call below needs for a trace of this
- * size, except llmv_attribute_sweep (llmv_sweep_workspace_size). */
+ * size, except llmv_attribute_sweep (llmv_sweep_workspace_size).  For 4097 to
+ * 2^22 tenants and at least 2^20 requests this includes a log of about 8 bytes
+ * per request, with which tenant sums beside shares are faster; a workspace of
+ * the size for more tenants (2^22 + 1) is without it and serves too. */
 size_t llmv_workspace_size(int64_t n_batches, int64_t n_requests, int32_t n_tenants);
 
 /* Bytes of device workspace llmv_attribute_sweep needs for a trace of this
@@ -169,7 +172,7 @@ int llmv_attribute_host(const llmv_trace *trace, const llmv_shape *shape,
  * first call there.  The call allocates nothing (no hipMalloc, no library
  * allocation); the caller still passes every input and output.  Outputs,
  * precision, ordering and errors are those of llmv_attribute; a trace whose
- * scratch (llmv_workspace_size of its sizes) exceeds the static array is
+ * scratch (llmv_workspace_size of its sizes, without the log) exceeds the static array is
  * refused with LLMV_EINVAL before anything is enqueued.  Every call on one
  * GPU shares that GPU's array: calls that overlap in time on one GPU (other
  * streams, other host threads) race and must be serialised by the caller.

@@ -15,6 +15,7 @@
 #include "llmv.h"
 #include "model.hpp"
 #include "step.hpp"
+#include "tenants.hpp"
 
 namespace llmv {
 // Scratch of llmv_attribute_noalloc, one copy per device (see llmv.h).
@@ -162,6 +163,69 @@ Layout layout(int64_t n, int32_t T) {
   if (n <= kShortMost) o += align_up((size_t)kShortGrid * kWaves * (kShortLong + 1) * sizeof(int64_t));
   L.total = o;
   return L;
+}
+
+// Tenant sums by k_tenant_split and k_tenant_fold: for more tenants than an
+// LDS histogram holds, at most kSplitTenants, and enough shares to be worth
+// the two launches (a call over 1.1M requests, 4097 tenants: 67 us, with the
+// tenant cache 79; over 2.5M, 2^20 tenants: 102 and 163).  Fewer shares, more tenants, calls that keep no shares
+// and a workspace without the log take the tenant cache.
+constexpr int64_t kSplitMin = 1 << 20;
+bool split_fits(int64_t n, int32_t T) {
+  return T > kHistLdsMax && T <= kSplitTenants && n >= kSplitMin;
+}
+
+// The split's log after a Layout ending at o.  A region holds its part of the
+// shares when they spread evenly and none is added in LDS, with room for the
+// spread of such counts.
+struct SplitLayout {
+  size_t counts, log, total;
+  int32_t cap;
+};
+SplitLayout split_layout(size_t o, int64_t n) {
+  SplitLayout S{};
+  const int64_t regions = (int64_t)kBins * kSplitGrid;
+  const double avg = (double)n / regions;
+  S.cap = (int32_t)((int64_t)(avg + 4 * std::sqrt(avg) + 2 * kBinChunk) / kBinChunk * kBinChunk);
+  S.counts = o;
+  o += align_up((size_t)regions * sizeof(uint32_t));
+  S.log = o;
+  o += align_up((size_t)regions * S.cap * sizeof(uint64_t));
+  S.total = o;
+  return S;
+}
+
+// Clears the n sums that atomics will add to.
+int zero_sums(double* x, int64_t n, hipStream_t st) {
+  const int64_t blocks = (n + kWG - 1) / kWG;
+  hipLaunchKernelGGL(k_zero_f64, dim3((unsigned)(blocks < 1024 ? blocks : 1024)), dim3(kWG), 0, st,
+                     x, n);
+  HIP_TRY(hipGetLastError(), "k_zero_f64 launch");
+  return LLMV_OK;
+}
+
+// Tenant sums of n shares through the split's log (split_fits).
+int run_split(const int32_t* tenant, const float* share, int64_t n, int32_t T, double* out,
+              char* base, const SplitLayout& S, int cus, hipStream_t st) {
+  int rc = zero_sums(out, T, st);
+  if (rc) return rc;
+  SplitArgs A{};
+  A.tenant = tenant;
+  A.share = share;
+  A.N = n;
+  A.map.bits = 13;
+  while ((int64_t)1 << A.map.bits < T) ++A.map.bits;
+  A.out = out;
+  A.counts = (uint32_t*)(base + S.counts);
+  A.log = (uint64_t*)(base + S.log);
+  A.cap = S.cap;
+  const int grid = cus < kSplitGrid ? cus : kSplitGrid;
+  hipLaunchKernelGGL(k_tenant_split, dim3(grid), dim3(kSplitWG), 0, st, A);
+  HIP_TRY(hipGetLastError(), "k_tenant_split launch");
+  hipLaunchKernelGGL(k_tenant_fold, dim3(kBins), dim3(kFoldWG),
+                     sizeof(double) << A.map.slot_bits(), st, A, grid, T);
+  HIP_TRY(hipGetLastError(), "k_tenant_fold launch");
+  return LLMV_OK;
 }
 
 // The what-if sweep's arrays after a Layout ending at o: slice table, exact
@@ -382,6 +446,19 @@ int run_tiles(int mode, const llmv_trace* tr, Params& P, const VT& V, int32_t T,
   const Layout L = layout(tr->n_requests, Tl);
   rc = check_ws(ws, ws_bytes, L.total);
   if (rc) return rc;
+  if (want_tenant && P.share && split_fits(tr->n_requests, T)) {
+    const SplitLayout S = split_layout(L.total, tr->n_requests);
+    if (ws_bytes >= S.total) {  // the shares first, then their tenant sums
+      Params Q = P;
+      Q.tenant = nullptr;
+      Q.tenant_sums = nullptr;
+      Q.n_tenants = 0;
+      rc = run_tiles(mode, tr, Q, V, 0, false, want_share, ws, ws_bytes, stream);
+      if (rc) return rc;
+      return run_split(tr->tenant, P.share, tr->n_requests, T, P.tenant_sums, (char*)ws, S, cus,
+                       stream);
+    }
+  }
   const int hist = !want_tenant ? HIST_NONE : (lds_hist(T) ? HIST_LDS : HIST_GLOBAL);
   const int rep = hist == HIST_LDS ? hist_replicas(T) : 1;
   const size_t dyn = hist == HIST_LDS ? (size_t)rep * (size_t)T * sizeof(double)
@@ -457,8 +534,8 @@ int run_tiles(int mode, const llmv_trace* tr, Params& P, const VT& V, int32_t T,
   if (rc) return rc;
   if (hist == HIST_GLOBAL) {
     // the atomics path accumulates into the output: clear it first
-    hipLaunchKernelGGL(k_zero_f64, dim3(16), dim3(kWG), 0, stream, P.tenant_sums, (int64_t)T);
-    HIP_TRY(hipGetLastError(), "k_zero_f64 launch");
+    rc = zero_sums(P.tenant_sums, T, stream);
+    if (rc) return rc;
   }
 
   if (g_ev_before) HIP_TRY(hipEventRecord(g_ev_before, stream), "hipEventRecord");
@@ -822,7 +899,9 @@ int llmv_shape_constants(const llmv_shape* shape, double S[4]) {
 size_t llmv_workspace_size(int64_t n_batches, int64_t n_requests, int32_t n_tenants) {
   (void)n_batches;
   const int64_t n = n_requests > 0 ? n_requests : 0;
-  return layout(n, n_tenants > 0 ? n_tenants : 0).total;
+  const int32_t T = n_tenants > 0 ? n_tenants : 0;
+  const size_t total = layout(n, T).total;
+  return split_fits(n, T) ? split_layout(total, n).total : total;
 }
 
 static size_t sweep_ws(int64_t n_batches, int64_t n_requests, int32_t n_tenants, bool ext) {
@@ -1013,8 +1092,8 @@ int llmv_tenant_sums(const int32_t* tenant, const float* share, int64_t n, int32
           : grid_for(n, cus, blocks_per_cu(k_tenant_hist<HIST_GLOBAL>, kCacheLds));
   if (!lds) {
     // the atomics path accumulates into the output: clear it first
-    hipLaunchKernelGGL(k_zero_f64, dim3(16), dim3(kWG), 0, s, tenant_sums, (int64_t)n_tenants);
-    HIP_TRY(hipGetLastError(), "k_zero_f64 launch");
+    rc = zero_sums(tenant_sums, n_tenants, s);
+    if (rc) return rc;
   }
   if (lds) {
     double* partials = (double*)(base + L.partials);

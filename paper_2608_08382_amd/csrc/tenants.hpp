@@ -1,0 +1,266 @@
+// tenants.hpp -- tenant sums of many shares over more tenants than an LDS
+// histogram holds (Sec. 2, Problem formulation: L_u, the sum of a tenant's
+// shares).
+//
+// k_tenant_split reads the shares once.  Each workgroup adds the frequent
+// tenants into an LDS table and logs every other share, binned by tenant, in
+// its own regions of the workspace; k_tenant_fold then adds up each bin, whose
+// tenants fit an LDS histogram.
+//
+// Why: a share that no LDS table takes used to be one device-scope fp64 atomic
+// on the output.  These complete in memory at about 22 G/s whatever their
+// locality, and 2^20 tenants under Zipf(1.2) send a sixth of the shares there.
+// Logged, such a share costs 8 bytes written and 8 read at stream rate, and
+// its add is an LDS atomic.  124.5M requests, 2^20 tenants, Zipf(1.2): 1516 us
+// in k_tiles with the tenant cache; now 368 us in k_tiles without tenants, 488
+// in the split and 50 in the fold (the whole call 1460 -> 900 us).
+#pragma once
+
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "kernels.hpp"
+
+namespace llmv {
+
+constexpr int kSplitWG = 1024;               // one workgroup per compute unit
+constexpr int kSplitGrid = 256;              // regions per bin: workgroups, at most
+constexpr int kSplitGroups = 2;              // 16-byte groups per thread and round
+constexpr int kSplitRound = kSplitWG * 4 * kSplitGroups;  // requests per round
+constexpr int kBinLog2 = 8;
+constexpr int kBins = 1 << kBinLog2;
+constexpr int kBinChunk = 16;                // entries written at once: 128 bytes
+constexpr int kBinCap = 2 * kBinChunk;       // entries a bin holds in LDS
+constexpr int kBinPitch = kBinCap + 1;       // odd: bins start in different banks
+constexpr int kTableLog2 = 12;
+constexpr int kTableSlots = 1 << kTableLog2;
+constexpr int kSplitSeen = 2048;             // words of the first-sight filter
+constexpr int kFoldWG = 1024;
+// Tenants of this path: a bin's histogram (T / kBins fp64 sums, T rounded up
+// to a power of two) takes at most 128 of the 160 KiB of LDS.
+constexpr int32_t kSplitTenants = 1 << 22;
+
+// Tenant ids are spread over the bins by an odd multiplier on the id without
+// its low three bits (a bijection on kBits - 3 bits), so that ids that are
+// frequent because they are low, or come in runs, do not share a bin; eight
+// consecutive ids stay together, so that the fold writes whole 64 bytes.
+constexpr uint32_t kMixMul = 0x9E3779B1u;
+constexpr uint32_t inverse_u32(uint32_t a) {
+  uint32_t x = a;  // correct to 3 bits; each step doubles them
+  for (int i = 0; i < 5; ++i) x *= 2u - a * x;
+  return x;
+}
+constexpr uint32_t kMixInv = inverse_u32(kMixMul);
+static_assert(kMixMul * kMixInv == 1u, "inverse modulo 2^32, so modulo every smaller power");
+
+struct SplitMap {
+  int bits;  // tenant ids are below 1 << bits, bits >= 13
+  __host__ __device__ uint32_t mask() const { return (1u << (bits - 3)) - 1u; }
+  __host__ __device__ int slot_bits() const { return bits - kBinLog2; }
+  __host__ __device__ uint32_t mixed(uint32_t t) const {
+    return ((((t >> 3) * kMixMul) & mask()) << 3) | (t & 7u);
+  }
+  __host__ __device__ uint32_t bin(uint32_t t) const { return mixed(t) >> slot_bits(); }
+  __host__ __device__ uint32_t slot(uint32_t t) const {
+    return mixed(t) & ((1u << slot_bits()) - 1u);
+  }
+  __host__ __device__ uint32_t tenant(uint32_t bin, uint32_t slot) const {
+    const uint32_t m = (bin << slot_bits()) | slot;
+    return ((((m >> 3) * kMixInv) & mask()) << 3) | (m & 7u);
+  }
+};
+
+struct SplitArgs {
+  const int32_t* tenant;  // [N], 16-byte aligned
+  const float* share;     // [N], 16-byte aligned
+  int64_t N;
+  SplitMap map;
+  double* out;            // [n_tenants], cleared before
+  uint64_t* log;          // region (bin, workgroup): cap entries at (bin*grid + wg)*cap
+  uint32_t* counts;       // entries of each region
+  int32_t cap;            // multiple of kBinChunk
+};
+
+// Workgroup w takes rounds w, w + grid, ... of kSplitRound requests.  A share
+// is added to its tenant's slot of a 4-way table in LDS (cache_add's rules: a
+// free way is taken on the tenant's second sight) or appended to its bin;
+// after each round the bins' whole chunks go to the regions, 128 bytes at a
+// time.  An entry that finds its bin full waits for that and tries again; one
+// that finds its region full is added to the output with an atomic.  The next
+// round's loads are in flight meanwhile.  Bound by
+// instructions: the LDS and the VALUs are each busy about half of the time (7.6
+// LDS and 66 VALU instructions per 64 shares).  Bins of 48 entries, written out
+// only when one is full, ran in 522 us: a bin with a frequent tenant that found
+// no slot fills every round.  Two workgroups of 512 threads with half the table
+// each: 569 us.
+__global__ __launch_bounds__(kSplitWG) void k_tenant_split(const SplitArgs A) {
+  __shared__ double s_sum[kTableSlots];
+  __shared__ __align__(16) int32_t s_tag[kTableSlots];
+  __shared__ uint32_t s_seen[kSplitSeen];
+  __shared__ uint64_t s_ent[kBins * kBinPitch];
+  __shared__ uint32_t s_cnt[kBins], s_out[kBins];
+  const int tid = threadIdx.x;
+  for (int i = tid; i < kTableSlots; i += kSplitWG) {
+    s_sum[i] = 0.0;
+    s_tag[i] = -1;
+  }
+  for (int i = tid; i < kSplitSeen; i += kSplitWG) s_seen[i] = 0u;
+  if (tid < kBins) s_cnt[tid] = s_out[tid] = 0u;
+  __syncthreads();
+
+  auto bucket = [&](int32_t t) {
+    return s_tag + 4 * (((uint32_t)t * 2654435761u) >> (32 - (kTableLog2 - 2)));
+  };
+  // the slot of tenant t, whose bucket's tags read as tg: its way, or a free
+  // one claimed on its second sight; -1 if it has none
+  auto slot_of = [&](int32_t t, v4i tg) {
+    int32_t* tb = bucket(t);
+    int w = tg.x == t ? 0 : (tg.y == t ? 1 : (tg.z == t ? 2 : (tg.w == t ? 3 : -1)));
+    if (w < 0 && (tg.x | tg.y | tg.z | tg.w) < 0) {
+      const uint32_t hs = ((uint32_t)t * 0x85ebca6bu) >> 16;
+      const uint32_t bit = 1u << (hs & 31u);
+      if (atomicOr(s_seen + (hs >> 5), bit) & bit) {
+        const int32_t ways[4] = {tg.x, tg.y, tg.z, tg.w};
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          if (w < 0 && ways[j] < 0) {
+            const int32_t old = atomicCAS(tb + j, -1, t);
+            if (old < 0 || old == t) w = j;
+          }
+        }
+      }
+    }
+    return w < 0 ? -1 : (int)(tb - s_tag) + w;
+  };
+  auto region = [&](uint32_t bin) {
+    return A.log + ((int64_t)bin * gridDim.x + blockIdx.x) * A.cap;
+  };
+  // entry `at` of this workgroup's region of a bin
+  auto log_entry = [&](uint64_t* reg, uint32_t at, uint64_t e) {
+    if (at < (uint32_t)A.cap)
+      reg[at] = e;
+    else
+      unsafeAtomicAdd(A.out + (uint32_t)e, (double)__uint_as_float((uint32_t)(e >> 32)));
+  };
+  v4i tv[kSplitGroups], sv[kSplitGroups];
+  auto load = [&](int64_t base) {
+    const int64_t m = min((int64_t)kSplitRound, A.N - base);
+    const auto bt = elem_rsrc(A.tenant + base, m), bs = elem_rsrc((const int32_t*)A.share + base, m);
+#pragma unroll
+    for (int g = 0; g < kSplitGroups; ++g) {
+      const int32_t i = 4 * (tid + kSplitWG * g);
+      tv[g] = load4<kNT>(bt, i);
+      sv[g] = load4<kNT>(bs, i);
+    }
+  };
+  const int64_t stride = (int64_t)gridDim.x * kSplitRound;
+  int64_t base = (int64_t)blockIdx.x * kSplitRound;
+  if (base < A.N) load(base);
+  for (; base < A.N; base += stride) {
+    int32_t t[4 * kSplitGroups];
+    float v[4 * kSplitGroups];
+    uint32_t pend = 0;  // shares still to log
+#pragma unroll
+    for (int g = 0; g < kSplitGroups; ++g) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        t[4 * g + j] = tv[g][j];
+        v[4 * g + j] = __builtin_bit_cast(float, (int)sv[g][j]);
+      }
+    }
+    const int64_t m = A.N - base;  // shares left, this round's first
+    if (base + stride < A.N) load(base + stride);
+    // the tags of all the round's shares first: a read after an atomic would
+    // wait for it
+    v4i tg[4 * kSplitGroups];
+#pragma unroll
+    for (int q = 0; q < 4 * kSplitGroups; ++q) tg[q] = *(const v4i*)bucket(t[q]);
+#pragma unroll
+    for (int q = 0; q < 4 * kSplitGroups; ++q) {
+      const int32_t i = 4 * (tid + kSplitWG * (q / 4)) + q % 4;
+      if (i < m) {
+        const int w = slot_of(t[q], tg[q]);
+        if (w >= 0)
+          atomicAdd(s_sum + w, (double)v[q]);
+        else
+          pend |= 1u << q;
+      }
+    }
+    bool again;
+    do {
+      uint32_t at[4 * kSplitGroups];
+#pragma unroll
+      for (int q = 0; q < 4 * kSplitGroups; ++q) {
+        at[q] = kBinCap;
+        if ((pend >> q) & 1u) at[q] = atomicAdd(&s_cnt[A.map.bin((uint32_t)t[q])], 1u);
+      }
+#pragma unroll
+      for (int q = 0; q < 4 * kSplitGroups; ++q) {
+        if (at[q] < (uint32_t)kBinCap) {
+          s_ent[A.map.bin((uint32_t)t[q]) * kBinPitch + at[q]] =
+              ((uint64_t)__float_as_uint(v[q]) << 32) | (uint32_t)t[q];
+          pend &= ~(1u << q);
+        }
+      }
+      __syncthreads();
+      // whole chunks to the regions: 16 lanes per bin
+      const int l = tid % kBinChunk;
+      for (int b = tid / kBinChunk; b < kBins; b += kSplitWG / kBinChunk) {
+        const uint32_t n = min(s_cnt[b], (uint32_t)kBinCap);
+        const uint32_t full = n & ~(uint32_t)(kBinChunk - 1);
+        if (full) {
+          uint64_t* ent = s_ent + b * kBinPitch;
+          uint64_t* reg = region(b);
+          const uint32_t at = s_out[b];
+          for (uint32_t o = 0; o < full; o += kBinChunk) log_entry(reg, at + o + l, ent[o + l]);
+          if ((uint32_t)l < n - full) ent[l] = ent[full + l];
+          if (l == 0) {
+            s_cnt[b] = n - full;
+            s_out[b] = at + full;
+          }
+        }
+      }
+      again = __syncthreads_or(pend != 0);
+    } while (again);
+  }
+  // what is left of the bins, the regions' counts, and the table
+  {
+    const int l = tid % kBinChunk;
+    for (int b = tid / kBinChunk; b < kBins; b += kSplitWG / kBinChunk) {
+      const uint32_t n = s_cnt[b], at = s_out[b];
+      if ((uint32_t)l < n) log_entry(region(b), at + l, s_ent[b * kBinPitch + l]);
+      if (l == 0) A.counts[b * gridDim.x + blockIdx.x] = min(at + n, (uint32_t)A.cap);
+    }
+  }
+  for (int i = tid; i < kTableSlots; i += kSplitWG)
+    if (s_tag[i] >= 0) unsafeAtomicAdd(A.out + s_tag[i], s_sum[i]);
+}
+
+// Workgroup b adds up bin b's regions in an LDS histogram of its tenants and
+// adds that to the output (no other workgroup has these tenants).  Bound by
+// reading the log.
+__global__ __launch_bounds__(kFoldWG) void k_tenant_fold(const SplitArgs A, int grid,
+                                                         int32_t n_tenants) {
+  extern __shared__ double s_fold[];  // [1 << slot_bits]
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const uint32_t b = blockIdx.x, n_slots = 1u << A.map.slot_bits();
+  for (uint32_t i = tid; i < n_slots; i += kFoldWG) s_fold[i] = 0.0;
+  __syncthreads();
+  for (int w = wave; w < grid; w += kFoldWG / 64) {
+    const uint32_t n = A.counts[b * grid + w];
+    const uint64_t* reg = A.log + ((int64_t)b * grid + w) * A.cap;
+#pragma unroll 4
+    for (uint32_t i = lane; i < n; i += 64) {
+      const uint64_t e = reg[i];
+      atomicAdd(s_fold + A.map.slot((uint32_t)e), (double)__uint_as_float((uint32_t)(e >> 32)));
+    }
+  }
+  __syncthreads();
+  for (uint32_t i = tid; i < n_slots; i += kFoldWG) {
+    const double v = s_fold[i];
+    const uint32_t t = A.map.tenant(b, i);
+    if (v != 0.0 && t < (uint32_t)n_tenants) A.out[t] += v;
+  }
+}
+
+}  // namespace llmv
