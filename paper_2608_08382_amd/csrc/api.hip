@@ -474,6 +474,7 @@ int run_tiles(int mode, const llmv_trace* tr, Params& P, const VT& V, int32_t T,
   P.big_seg = nullptr;
 
   const int64_t cap = tile_cap(mode, hist);
+  P.long_min = (int32_t)cap;
   // a batch larger than a tile needs more than cap - 4 requests
   const bool longs = tr->n_requests > cap - 4;
   if ((mode == MODE_ATTR || mode == MODE_EXT) && hist != HIST_GLOBAL && longs &&
@@ -517,6 +518,8 @@ int run_tiles(int mode, const llmv_trace* tr, Params& P, const VT& V, int32_t T,
   const bool long_mean = tr->n_requests > tr->n_batches * (int64_t)cap;
   const ChunkMap cm = long_mean ? chunk_map(tr->n_requests, grid * kWaves, false, cap, 8, 2)
                                 : chunk_map(tr->n_requests, grid * kWaves, true, cap);
+  // (the list has room for every batch then: fewer than n_requests / cap)
+  if (long_mean && mode != MODE_EXT) P.long_min = kLongFew;
   P.wg_first = wg_first;
   P.split_by_count = 0;
   P.claims = (unsigned long long*)(base + L.claims);

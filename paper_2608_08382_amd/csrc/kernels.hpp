@@ -90,7 +90,8 @@ struct ChunkMap {
 constexpr int kClaimGroups = 8;
 constexpr int kSegCounter = kClaimGroups;
 constexpr int kLongCounter = kClaimGroups + 1;
-constexpr int kCounters = kClaimGroups + 2;
+constexpr int kLongClaims = kClaimGroups + 2;  // claims of listed batches, in kClaimGroups groups (k_long)
+constexpr int kCounters = kLongClaims + kClaimGroups;
 
 // MODE_ATTR: latency, regime, share, tenant sums of one (shape, theta).
 // MODE_FEAT: the feature rows.  MODE_EXT: the outputs of MODE_ATTR under the
@@ -145,6 +146,16 @@ constexpr int64_t kShortMost = 64 * 64 * kVecWide;
 constexpr int kShortGrid = (int)((kShortMost + kCapShort * kWaves - 1) / (kCapShort * kWaves));
 constexpr int kShortLong = 4;  // long batches of a wave's chunk, at most (run_short)
 
+// Where the mean batch is larger than a tile, batches of more than kLongFew
+// slots are listed, not only those larger than a tile: among long batches a tile
+// seldom holds more than one, and a wave that alternates between tiles and
+// listing waits for an offsets window at every step.  115M requests in steps of
+// 512 to 4096: k_tiles 221 -> 33 us, k_long 350 -> 404, the call 562 -> 448 (519
+// with 1024 slots).  Not under the extended model, whose tile kernel the test
+// for it slows down by 0.5% where steps are short.
+constexpr int kLongFew = 448;
+template <int MODE> constexpr bool kLongFewMode = MODE != MODE_EXT;
+
 // A batch listed for the segment kernels: its index and exact sums (sum p,
 // sum c, sum p^2, count of c == 0), accumulated by k_big_sums.
 struct BigEntry {
@@ -189,6 +200,9 @@ struct Params {
   // Short trace: kShortLong entries per wave, the waves' counts at long_count.
   int64_t* long_list;
   unsigned long long* long_count;
+  // Batches of more than this many slots are listed (the tile's slots, or
+  // fewer where most requests lie in such batches: kLongFew).
+  int32_t long_min;
   int64_t phase_bit;          // added to |B| in bsums row 0 of a prefill batch (0: none)
   int32_t n_tenants;
   int32_t hist_rep;         // MODE_ATTR, HIST_LDS: histogram replicas (1, 2 or 4)
@@ -729,9 +743,9 @@ __device__ __forceinline__ void load_round(const Params& P, int64_t o, int64_t m
   }
 }
 
-// One batch too large for a wave tile (k_long), walked by one wave in
+// One listed batch (k_long), walked by one wave in
 // rounds of kRoundSlots slots from ra (its first request rounded down to 4).
-// A batch of two rounds is held whole in registers: its requests are read
+// A batch of one or two rounds is held whole in registers: its requests are read
 // once, as in a tile.  A longer one keeps its first round in registers and
 // streams the others twice: for the exact sums, then for the per-request
 // outputs.  wk, wk4: the wave's LDS words for the batch constants.
@@ -746,8 +760,8 @@ __device__ __forceinline__ void long_batch(const Params& P, const typename VarsO
   const int lane = threadIdx.x & 63;
   const int64_t ra = uni(rs & ~(int64_t)3);
   const int32_t xf = uni((int32_t)(rs - ra));  // first slot of the batch
-  const int32_t L = uni((int32_t)(re - ra));   // slots up to its end (> kRoundSlots)
-  const int32_t nr = (L + kRoundSlots - 1) / kRoundSlots;  // rounds, at least 2
+  const int32_t L = uni((int32_t)(re - ra));   // slots up to its end
+  const int32_t nr = (L + kRoundSlots - 1) / kRoundSlots;  // rounds
   const int32_t x0 = lane * kVec;
   // slots of round r: [r*kRoundSlots, min((r+1)*kRoundSlots, L)), from request o(r)
   auto o_of = [&](int32_t r) { return ra + (int64_t)r * kRoundSlots; };
@@ -831,7 +845,11 @@ __device__ __forceinline__ void long_batch(const Params& P, const typename VarsO
 
   int32_t p0[kVec], c0[kVec], t0[kVec];
   load_round<VEC, TEN>(P, o_of(0), m_of(0), x0, p0, c0, t0);
-  if (nr == 2) {
+  if (nr == 1) {
+    add(p0, c0, 0);
+    model();
+    if constexpr (OUT) out(p0, c0, t0, 0);
+  } else if (nr == 2) {
     int32_t p1[kVec], c1[kVec], t1[kVec];
     // a second round of at most 4 slots (a batch just over a tile) sits in
     // lane 0's first group: one load per array instead of VEC/4 (not with
@@ -956,6 +974,7 @@ __global__ __launch_bounds__(kWG) void k_tiles(const Params P,
   __shared__ WaveLds<VEC> s_wave[kWaves];
   constexpr bool STAGE = kStaged<MODE, SHARE>;
   constexpr bool EXT = MODE == MODE_EXT;
+  constexpr bool FEW = kLongFewMode<MODE> && !SHORT;
   constexpr bool RSUM = kCrossSum<MODE>;
   // extended model, per wave: sum p*c and the share constant k4 of each batch
   __shared__ uint64_t s_rsum[RSUM ? kWaves * kTileBatches : 1];
@@ -1068,14 +1087,16 @@ __global__ __launch_bounds__(kWG) void k_tiles(const Params P,
       const int64_t ra = r0 & ~(int64_t)3;
       const int64_t rel = wv - ra;
       const uint64_t fits = __ballot(lane >= 1 && lane <= lim && rel <= kTile);
-      const int32_t count = uni((int32_t)__builtin_popcountll(fits));  // a prefix of lanes
+      int32_t count = uni((int32_t)__builtin_popcountll(fits));  // a prefix of lanes
       // batches consumed by this step: the tile's, or (count == 0) the run of
-      // batches from b each larger than a tile (lane j < lim: batch b+j)
+      // batches from b each to be listed (lane j < lim: batch b+j)
       int32_t adv = count;
-      if (count == 0) {
+      if (count == 0 || (FEW && P.long_min < kTile)) {
         const int64_t end = __shfl(wv, min(lane + 1, 63), 64);
-        const uint64_t alone = __ballot(lane < lim && end - (wv & ~(int64_t)3) > kTile);
-        adv = uni((int32_t)__builtin_ctzll(~alone));  // at least 1: batch b is one
+        const int64_t most = FEW ? P.long_min : kTile;
+        const uint64_t alone = __ballot(lane < lim && end - (wv & ~(int64_t)3) > most);
+        if (alone) count = min(count, uni((int32_t)__builtin_ctzll(alone)));
+        adv = count ? count : uni((int32_t)__builtin_ctzll(~alone));  // at least 1: batch b is one
       }
       const int64_t e = b + adv;
       const int64_t r1 = uni(readlane_i64(wv, adv));
@@ -1517,11 +1538,35 @@ __global__ __launch_bounds__(kWG, 2) void k_long(const Params P, const typename 
   __syncthreads();
 
   float* stage = s_stage + (STAGE ? wave * 64 * kStagePitch : 0);
-  for (uint64_t k = (uint64_t)blockIdx.x * kWaves + wave; k < n_long;
-       k += (uint64_t)gridDim.x * kWaves) {
+  // The first n_fix entries go round-robin over the waves; the others, a quarter
+  // of the list and 4 to 8 per wave, are claimed (as the tile kernel's chunks
+  // are), each claim issued while the batch before it is walked.
+  const uint64_t waves = (uint64_t)gridDim.x * kWaves, w = (uint64_t)blockIdx.x * kWaves + wave;
+  uint64_t n_fix = n_long;
+  if (P.claims) {
+    const uint64_t q = min(max(n_long / 4, 4 * waves), 8 * waves);
+    n_fix = n_long - min(n_long, q);
+  }
+  const int cg = (int)(w % kClaimGroups);
+  auto claim_next = [&](uint64_t k) {  // claimed while entry k is walked
+    unsigned long long c = 0;
+    if (k + waves >= n_fix && P.claims && lane == 0) c = atomicAdd(P.claims + kLongClaims + cg, 1ull);
+    return c;
+  };
+  uint64_t k = w;
+  if (k >= n_fix) {
+    const unsigned long long c = P.claims ? claim_next(n_fix) : n_long;
+    k = n_fix + cg + readlane_u64(c, 0) * kClaimGroups;
+  }
+  while (k < n_long) {
+    const unsigned long long c = claim_next(k);
     const int64_t b = uni(P.long_list[k]);
     const int64_t rs = uni(P.off[b]), re = uni(P.off[b + 1]);
     long_batch<MODE, HIST, SHARE, VEC>(P, V, s_k[wave], &s_k4[wave], stage, b, rs, re, s_hist_lane);
+    if (k + waves < n_fix)
+      k += waves;
+    else
+      k = P.claims ? n_fix + cg + readlane_u64(c, 0) * kClaimGroups : n_long;
   }
 
   if constexpr (MODE == MODE_ATTR) {

@@ -1,0 +1,65 @@
+"""Traces whose mean batch is larger than a wave tile, where batches of more
+than 448 slots are listed and claimed: edges of the listing (447 to 452 slots,
+whatever the batch's alignment), of a tile and of two, empty and one-request
+batches between them, and more listed batches than are claimed, against the
+oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import tracegen
+from paper_2608_08382_amd import llmv
+
+pytestmark = pytest.mark.gpu
+
+EDGES = [0, 1, 2, 444, 445, 446, 447, 448, 449, 450, 451, 1535, 1536, 1788, 1789, 1790, 1791, 1792,
+         1793, 3580, 3583, 3584, 3585, 5377, 7000, 9001]
+
+
+def _sizes(rng, kind):
+    if kind == "edges":
+        return np.concatenate([rng.permutation(EDGES) for _ in range(6)])
+    if kind == "runs":  # runs of small batches between large ones
+        return np.concatenate([np.concatenate([np.full(70, 30), np.full(40, 6000), [0, 448, 449]])
+                               for _ in range(4)])
+    if kind == "listed":  # a listed batch per segment list too
+        return np.concatenate([rng.permutation(EDGES), [114_689, 500, 120_001], rng.permutation(EDGES)])
+    return rng.integers(1900, 2100, 9000)  # "many": more batches than the claimed part takes
+
+
+@pytest.mark.parametrize("kind", ["edges", "runs", "listed", "many"])
+@pytest.mark.parametrize("n_tenants", [1, 1000, 5000])
+def test_long_mean(kind, n_tenants):
+    rng = np.random.default_rng(7)
+    off = np.concatenate([[0], np.cumsum(_sizes(rng, kind))]).astype(np.int64)
+    n = int(off[-1])
+    assert n > 1792 * (len(off) - 1) and n > 114_688
+    pre = np.repeat(rng.random(len(off) - 1) < 0.3, np.diff(off))
+    p = np.where(pre, rng.integers(1, 2000, n), 1).astype(np.int32)
+    c = np.where(pre, 0, rng.integers(1, 30000, n)).astype(np.int32)
+    t = rng.integers(0, n_tenants, n).astype(np.int32)
+    tr = llmv.DeviceTrace.from_host(off, p, c, t)
+    shape = tracegen.SHAPES["llama3.1-8b"]
+    for ext in (False, True):
+        co = (tracegen.ext_coeffs if ext else tracegen.base_coeffs)(5)
+        got = (llmv.attribute_ext if ext else llmv.attribute)(tr, shape, co, n_tenants)
+        ref = (oracle.attribute_ext if ext else oracle.attribute)(off, p, c, t, shape, co, n_tenants)
+        tie = np.abs(ref["TM"] - ref["TC"]) <= 1e-6 * np.maximum(ref["TM"], ref["TC"])
+        assert np.all((got["regime"].cpu().numpy() == ref["regime"]) | tie) and not tie[np.diff(off) > 0].any()
+        for k, r in (("latency", "T"), ("share", "share"), ("tenant_sums", "tenant_sums")):
+            g = got[k].cpu().numpy().astype(np.float64)
+            # an fp32 rounding of an fp64 value, or 4 fp32 operations of
+            # nonnegative terms on fp32-rounded constants
+            assert np.all(np.abs(g - ref[r]) <= 10 * 2.0 ** -24 * np.abs(ref[r])), k
+    usage = llmv.attribute(tr, shape, tracegen.base_coeffs(5), n_tenants, ("latency", "tenant_sums"))
+    base = llmv.attribute(tr, shape, tracegen.base_coeffs(5), n_tenants)
+    assert torch.equal(usage["latency"], base["latency"])
+    for ext in (False, True):
+        sums, phase = (x.cpu().numpy() for x in llmv.batch_sums(tr, ext=ext))
+        seg = lambda x: np.diff(np.concatenate([[0], np.cumsum(x.astype(np.int64))])[off])
+        want = [np.diff(off), seg(p), seg(c), seg(p.astype(np.int64) * p)]
+        want += [seg(p.astype(np.int64) * c)] if ext else []
+        assert np.array_equal(sums, np.stack(want))
+    x_req, _ = llmv.features(tr, shape)
+    assert np.array_equal(x_req[4].cpu().numpy(), np.repeat(np.diff(off), np.diff(off)).astype(np.float32))
