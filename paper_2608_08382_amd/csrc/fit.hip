@@ -16,6 +16,7 @@ using namespace llmv::host;
 namespace {
 
 constexpr int kFitMaxGrid = 1024;
+static_assert(kAccGrid<5> <= kFitMaxGrid && kAccGrid<7> <= kFitMaxGrid, "rows of partials");
 constexpr int kMaxRounds = 1024;
 constexpr int64_t kFitMaxBatches = (int64_t)1 << 31;
 
@@ -102,9 +103,10 @@ int fit_run(const int64_t* sums, const uint8_t* phase, int64_t n_batches, const 
   HIP_TRY(hipGetLastError(), "k_fit_init launch");
   FitShape F{};
   for (int k = 0; k < 6; ++k) F.S[k] = M.S[k];
-  const int grid = fit_grid(n_batches);
+  const int64_t all = (n_batches + kAccWG<NC> - 1) / kAccWG<NC>;
+  const int grid = all < 1 ? 1 : (all > kAccGrid<NC> ? kAccGrid<NC> : (int)all);
   for (int r = 0; r < rounds; ++r) {
-    hipLaunchKernelGGL(k_fit_accum<NC>, dim3(grid), dim3(kFitWG), 0, s, sums, phase, n_batches, F,
+    hipLaunchKernelGGL(k_fit_accum<NC>, dim3(grid), dim3(kAccWG<NC>), 0, s, sums, phase, n_batches, F,
                        y, (const double*)theta, partials);
     HIP_TRY(hipGetLastError(), "k_fit_accum launch");
     hipLaunchKernelGGL(k_fit_solve<NC>, dim3(1), dim3(kReduceWG), 0, s,

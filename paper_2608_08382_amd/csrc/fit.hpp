@@ -91,8 +91,22 @@ __device__ __forceinline__ void fit_features(const double* S, int64_t n, int64_t
   }
 }
 
-__device__ __forceinline__ double wave_sum_f64(double x) {
-  for (int m = 32; m >= 1; m >>= 1) x += __shfl_xor(x, m, 64);
+// The sum over the wave in lane 63, through DPP (no LDS): each 16-lane row scanned, then
+// carried into the rows above; lanes without a source add 0.
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ double dpp_f64(double v) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, ROW_MASK, 0xf, false);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, ROW_MASK, 0xf, false);
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+__device__ __forceinline__ double wave_sum_dpp(double x) {
+  x += dpp_f64<0x111, 0xf>(x);  // row_shr:1
+  x += dpp_f64<0x112, 0xf>(x);  // row_shr:2
+  x += dpp_f64<0x114, 0xf>(x);  // row_shr:4
+  x += dpp_f64<0x118, 0xf>(x);  // row_shr:8
+  x += dpp_f64<0x142, 0xa>(x);  // row_bcast:15 into rows 1 and 3
+  x += dpp_f64<0x143, 0xc>(x);  // row_bcast:31 into rows 2 and 3
   return x;
 }
 
@@ -124,79 +138,121 @@ __device__ __forceinline__ BatchRegs load_batch(const int64_t* __restrict__ sums
 
 // Per-workgroup sums of the normal equations of each set under the current
 // coefficients theta (device [4*NC]): partials[block][set*kSet + k].
-// A workgroup walks chunks of kFitWG batches: the chunk is loaded once,
-// coalesced (the next chunk's loads are issued before the current one is
-// processed) and staged in LDS; wave w then folds the chunk's batches of set
-// w (phase w/2, segment w%2) into kSet register accumulators per lane.
+// A workgroup walks chunks of one batch per thread, the next chunk's
+// loads issued before the current one is processed.  A thread forms its batch's
+// features and segment once; the batches are then sorted by set in LDS (in
+// batch order within a set), and the waves w with w % 4 == k fold set k's into
+// kSet register accumulators per lane.  Few and large workgroups, because
+// k_fit_solve adds their rows on one compute unit: with 1024 workgroups of four
+// waves, each evaluating every batch and keeping its own set's, 1M batches
+// (41 MB) took 26 us here and 16.8 in the solve; now 25.6 and 10.4, four rounds
+// 171 -> 143 us, under the extended model 294 -> 202.  The sums are fused
+// multiply-adds: the products are not rounded.  What is left here is the
+// latency of a few chunks per workgroup: workgroups of 1024 threads spill (65
+// us; the solve then takes 7.6).
+template <int NC> constexpr int kAccWG = 512;
+template <int NC> constexpr int kAccGrid = 256 * 1024 / kAccWG<NC>;  // at most
 template <int NC>
-__global__ __launch_bounds__(kFitWG) void k_fit_accum(const int64_t* __restrict__ sums,
+__global__ __launch_bounds__((kAccWG<NC>)) void k_fit_accum(const int64_t* __restrict__ sums,
                                                       const uint8_t* __restrict__ phase,
                                                       int64_t nB, const FitShape F,
                                                       const double* __restrict__ y,
                                                       const double* __restrict__ theta,
                                                       double* __restrict__ partials) {
-  static_assert(kFitWG == 4 * 64, "one wave per (phase, segment) set");
+  constexpr int kWG = kAccWG<NC>, kWaves = kWG / 64, kTeam = kWaves / 4;  // kTeam waves per set
+  static_assert(kWaves % 4 == 0, "as many waves for every set");
   using Cols = FitCols<NC>;
-  constexpr int kTri = Cols::kTri, kSet = Cols::kSet;
-  __shared__ int64_t s_n[kFitWG], s_P[kFitWG], s_C[kFitWG], s_Q[kFitWG];
-  __shared__ int64_t s_R[NC == 7 ? kFitWG : 1];
-  __shared__ double s_y[kFitWG];
-  __shared__ int s_ph[kFitWG];
-  const int tid = threadIdx.x, lane = tid & 63, set = tid >> 6;
-  const int set_phase = set >> 1, set_seg = set & 1;
-  double th[2 * NC];  // the two segment sets of this wave's phase
-#pragma unroll
-  for (int i = 0; i < 2 * NC; ++i) th[i] = theta[set_phase * 2 * NC + i];
+  constexpr int kTri = Cols::kTri, kSet = Cols::kSet, kFlags = Cols::kFlags - 1;
+  __shared__ double s_X[NC - 1][kWG], s_y[kWG];  // features 1.. and y, by set
+  __shared__ uint32_t s_flag[kWG];                  // identifiability, a bit each
+  __shared__ uint32_t s_cnt[kWaves][4];           // batches of each wave and set
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   double acc[kSet];
 #pragma unroll
   for (int i = 0; i < kSet; ++i) acc[i] = 0.0;
 
-  const int64_t stride = (int64_t)gridDim.x * kFitWG;
-  int64_t base = (int64_t)blockIdx.x * kFitWG;
-  BatchRegs cur = load_batch<NC>(sums, phase, y, nB, base + tid);
+  const int64_t stride = (int64_t)gridDim.x * kWG;
+  int64_t base = (int64_t)blockIdx.x * kWG;
+  BatchRegs next = load_batch<NC>(sums, phase, y, nB, base + tid);
   for (; base < nB; base += stride) {
-    s_n[tid] = cur.n;
-    s_P[tid] = cur.P;
-    s_C[tid] = cur.C;
-    s_Q[tid] = cur.Q;
-    if constexpr (NC == 7) s_R[tid] = cur.R;
-    s_y[tid] = cur.y;
-    s_ph[tid] = cur.ph;
-    __syncthreads();
-    cur = load_batch<NC>(sums, phase, y, nB, base + stride + tid);  // next chunk, in flight
+    const BatchRegs cur = next;
+    next = load_batch<NC>(sums, phase, y, nB, base + stride + tid);
+    double X[NC];
+    fit_features<NC>(F.S, cur.n, cur.P, cur.C, cur.Q, cur.R, X);
+    // Roofline max of the two segments; ties stay memory-bound.
+    int set = -1;
+    if (cur.ph >= 0) {
+      double th[2 * NC];
 #pragma unroll
-    for (int k = 0; k < kFitWG / 64; ++k) {
-      const int i = k * 64 + lane;
-      if (s_ph[i] != set_phase) continue;
-      const int64_t n = s_n[i], P = s_P[i], C = s_C[i], Q = s_Q[i];
-      const int64_t R = NC == 7 ? s_R[i] : 0;
-      double X[NC];
-      fit_features<NC>(F.S, n, P, C, Q, R, X);
-      // Roofline max of the two segments; ties stay memory-bound.
-      const int seg = fit_eq<NC>(th + NC, X) > fit_eq<NC>(th, X) ? 1 : 0;
-      if (seg != set_seg) continue;
+      for (int i = 0; i < 2 * NC; ++i) th[i] = cur.ph == 0 ? theta[i] : theta[2 * NC + i];
+      set = 2 * cur.ph + (fit_eq<NC>(th + NC, X) > fit_eq<NC>(th, X) ? 1 : 0);
+    }
+    uint32_t rank = 0;  // among the wave's batches of the set
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const uint64_t in = __ballot(set == k);
+      if (set == k) rank = __builtin_popcountll(in & ((1ull << lane) - 1ull));
+      if (lane == 0) s_cnt[wave][k] = __builtin_popcountll(in);
+    }
+    __syncthreads();
+    // first entry of each set (in set order), and of this wave's batches of it
+    const int own = wave % 4;  // the set this wave folds
+    uint32_t first = 0, mine = 0, at = 0;  // of that set: its first entry and count
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      uint32_t total = 0, before = 0;
+#pragma unroll
+      for (int w = 0; w < kWaves; ++w) {
+        if (w == wave) before = total;
+        total += s_cnt[w][k];
+      }
+      if (k < own) first += total;
+      if (k == own) mine = total;
+      if (k < set) at += total;
+      if (k == set) at += before;
+    }
+    if (set >= 0) {
+      const uint32_t i = at + rank;
+#pragma unroll
+      for (int k = 1; k < NC; ++k) s_X[k - 1][i] = X[k];
+      s_y[i] = cur.y;
+      uint32_t f = (cur.Q != cur.P ? 1u : 0u) | (cur.C != 0 ? 2u : 0u);
+      if constexpr (NC == 7) f |= (cur.R != cur.C ? 4u : 0u) | (cur.P != cur.n ? 8u : 0u);
+      s_flag[i] = f;
+    }
+    __syncthreads();
+    for (uint32_t i = first + (wave / 4) * 64 + lane; i < first + mine; i += kTeam * 64) {
+      X[0] = F.S[0];
+#pragma unroll
+      for (int k = 1; k < NC; ++k) X[k] = s_X[k - 1][i];
       const double yb = s_y[i];
+      const uint32_t f = s_flag[i];
       int q = 0;
 #pragma unroll
       for (int a = 0; a < NC; ++a)
 #pragma unroll
-        for (int c = a; c < NC; ++c) acc[q++] += X[a] * X[c];
+        for (int c = a; c < NC; ++c, ++q) acc[q] = fma(X[a], X[c], acc[q]);
 #pragma unroll
-      for (int a = 0; a < NC; ++a) acc[kTri + a] += X[a] * yb;
-      acc[kTri + NC + 0] += 1.0;
-      acc[kTri + NC + 1] += Q != P ? 1.0 : 0.0;
-      acc[kTri + NC + 2] += C != 0 ? 1.0 : 0.0;
-      if constexpr (NC == 7) {
-        acc[kTri + NC + 3] += R != C ? 1.0 : 0.0;
-        acc[kTri + NC + 4] += P != n ? 1.0 : 0.0;
-      }
+      for (int a = 0; a < NC; ++a) acc[kTri + a] = fma(X[a], yb, acc[kTri + a]);
+      acc[kTri + NC] += 1.0;
+#pragma unroll
+      for (int k = 0; k < kFlags; ++k) acc[kTri + NC + 1 + k] += (f >> k) & 1u ? 1.0 : 0.0;
     }
-    __syncthreads();
+    // (the next chunk's counts are written after its first ballots, its entries
+    // after its first barrier)
   }
+  __shared__ double s_red[kWaves][kSet];
 #pragma unroll
   for (int i = 0; i < kSet; ++i) {
-    const double t = wave_sum_f64(acc[i]);
-    if (lane == 0) partials[(int64_t)blockIdx.x * Cols::kVals + set * kSet + i] = t;
+    const double t = wave_sum_dpp(acc[i]);
+    if (lane == 63) s_red[wave][i] = t;
+  }
+  __syncthreads();
+  for (int i = tid; i < Cols::kVals; i += kWG) {
+    double t = 0.0;
+#pragma unroll
+    for (int w = 0; w < kTeam; ++w) t += s_red[4 * w + i / kSet][i % kSet];
+    partials[(int64_t)blockIdx.x * Cols::kVals + i] = t;
   }
 }
 
@@ -207,13 +263,28 @@ __global__ __launch_bounds__(kFitWG) void k_fit_accum(const int64_t* __restrict_
 template <int NCOLS>
 __device__ __forceinline__ void reduce_columns(const double* __restrict__ partials, int grid,
                                                double* red, double* tot) {
-  constexpr int PARTS = kReduceWG / NCOLS;
+  constexpr int PARTS = kReduceWG / NCOLS, kAhead = 32;
   const int t = threadIdx.x;
   if (t < PARTS * NCOLS) {
     const int col = t % NCOLS, part = t / NCOLS;
     double s = 0.0;
-#pragma unroll 8
-    for (int blk = part; blk < grid; blk += PARTS) s += partials[(int64_t)blk * NCOLS + col];
+    // kAhead rows loaded at a time: the sum is bound by the loads' latency
+    int blk = part;
+    for (; blk + (kAhead - 1) * PARTS < grid; blk += kAhead * PARTS) {
+      double v[kAhead];
+#pragma unroll
+      for (int i = 0; i < kAhead; ++i) v[i] = partials[(int64_t)(blk + i * PARTS) * NCOLS + col];
+#pragma unroll
+      for (int i = 0; i < kAhead; ++i) s += v[i];
+    }
+    if (blk < grid) {
+      double v[kAhead];
+#pragma unroll
+      for (int i = 0; i < kAhead; ++i)
+        v[i] = blk + i * PARTS < grid ? partials[(int64_t)(blk + i * PARTS) * NCOLS + col] : 0.0;
+#pragma unroll
+      for (int i = 0; i < kAhead; ++i) s += v[i];
+    }
     red[part * NCOLS + col] = s;
   }
   __syncthreads();
@@ -373,8 +444,8 @@ __device__ __forceinline__ void block_partials(const double acc[kMetricVals],
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
   for (int i = 0; i < kMetricVals; ++i) {
-    const double t = wave_sum_f64(acc[i]);
-    if (lane == 0) s_red[wave][i] = t;
+    const double t = wave_sum_dpp(acc[i]);
+    if (lane == 63) s_red[wave][i] = t;
   }
   __syncthreads();
   if (threadIdx.x < kMetricVals) {
@@ -454,8 +525,11 @@ __global__ __launch_bounds__(kFitWG) void k_fit_metrics1(const int64_t* __restri
   const unsigned int counted = counted_selections(pre0);
   double acc[kMetricVals] = {0, 0, 0, 0, 0, 0, 0, 0};
   const int64_t stride = (int64_t)gridDim.x * kFitWG;
-  for (int64_t b = (int64_t)blockIdx.x * kFitWG + threadIdx.x; b < nB; b += stride) {
-    const BatchRegs r = load_batch<NC>(sums, phase, y, nB, b);
+  int64_t b = (int64_t)blockIdx.x * kFitWG + threadIdx.x;
+  BatchRegs next = load_batch<NC>(sums, phase, y, nB, b);
+  for (; b < nB; b += stride) {
+    const BatchRegs r = next;
+    next = load_batch<NC>(sums, phase, y, nB, b + stride);
     float e = __builtin_nanf("");
     if (r.ph >= 0) {
       const double yhat = predict<NC>(A, r);
@@ -499,8 +573,11 @@ __global__ __launch_bounds__(kFitWG) void k_fit_metrics2(const int64_t* __restri
                           n0 + n1 > 0 ? (tot1[1] + tot1[5]) / (n0 + n1) : 0.0};
   double acc[kMetricVals] = {0, 0, 0, 0, 0, 0, 0, 0};
   const int64_t stride = (int64_t)gridDim.x * kFitWG;
-  for (int64_t b = (int64_t)blockIdx.x * kFitWG + threadIdx.x; b < nB; b += stride) {
-    const BatchRegs r = load_batch<NC>(sums, phase, y, nB, b);
+  int64_t b = (int64_t)blockIdx.x * kFitWG + threadIdx.x;
+  BatchRegs next = load_batch<NC>(sums, phase, y, nB, b);
+  for (; b < nB; b += stride) {
+    const BatchRegs r = next;
+    next = load_batch<NC>(sums, phase, y, nB, b + stride);
     if (r.ph < 0) continue;
     const double res = r.y - predict<NC>(A, r);
 #pragma unroll
