@@ -355,6 +355,16 @@ template <> struct TilePick<ExtModel> {
   }
 };
 
+// The tile kernel of attribution under Eq. 1 where the mean batch is larger
+// than a tile (kLongFew).
+TileKernel pick_few(int hist, bool share) {
+#define LLMV_FEW(HIST, SHARE) k_tiles<MODE_ATTR, HIST, SHARE, kVecOf<MODE_ATTR, HIST>, true>
+  if (hist == HIST_NONE) return share ? LLMV_FEW(HIST_NONE, true) : LLMV_FEW(HIST_NONE, false);
+  if (hist == HIST_LDS) return share ? LLMV_FEW(HIST_LDS, true) : LLMV_FEW(HIST_LDS, false);
+  return share ? LLMV_FEW(HIST_GLOBAL, true) : LLMV_FEW(HIST_GLOBAL, false);
+#undef LLMV_FEW
+}
+
 // The two kernels of a short trace (attribution, no tenant cache).
 template <int MODE, int HIST, bool SHARE, typename VT>
 int launch_short(const Params& P, const VT& V, int grid, size_t dyn, hipStream_t st) {
@@ -463,7 +473,7 @@ int run_tiles(int mode, const llmv_trace* tr, Params& P, const VT& V, int32_t T,
   const int rep = hist == HIST_LDS ? hist_replicas(T) : 1;
   const size_t dyn = hist == HIST_LDS ? (size_t)rep * (size_t)T * sizeof(double)
                      : (hist == HIST_GLOBAL ? kCacheLds : 0);
-  const auto kern = TilePick<VT>::get(mode, hist, want_share);
+  auto kern = TilePick<VT>::get(mode, hist, want_share);
   const auto klong = LongPick<VT>::get(mode, hist, want_share);
   P.hist_rep = rep;
   char* base = (char*)ws;
@@ -474,7 +484,6 @@ int run_tiles(int mode, const llmv_trace* tr, Params& P, const VT& V, int32_t T,
   P.big_seg = nullptr;
 
   const int64_t cap = tile_cap(mode, hist);
-  P.long_min = (int32_t)cap;
   // a batch larger than a tile needs more than cap - 4 requests
   const bool longs = tr->n_requests > cap - 4;
   if ((mode == MODE_ATTR || mode == MODE_EXT) && hist != HIST_GLOBAL && longs &&
@@ -506,6 +515,10 @@ int run_tiles(int mode, const llmv_trace* tr, Params& P, const VT& V, int32_t T,
     return LLMV_OK;
   }
 
+  const bool long_mean = tr->n_requests > tr->n_batches * (int64_t)cap;
+  // (the long list has room for every batch then: fewer than n_requests / cap)
+  if constexpr (std::is_same<VT, NoVars>::value)
+    if (long_mean && mode == MODE_ATTR) kern = pick_few(hist, want_share);
   const int64_t grid = grid_for(tr->n_requests, cus, blocks_per_cu(kern, dyn));
   int64_t* wg_first = (int64_t*)(base + L.wg_first);
   const int n_chunks = want_tenant ? (T + kTenantChunk - 1) / kTenantChunk : 0;
@@ -515,11 +528,8 @@ int run_tiles(int mode, const llmv_trace* tr, Params& P, const VT& V, int32_t T,
   // microseconds, and chunk setups and claims (device-scope atomics) cost
   // more than the balance they buy.  One static chunk per wave over all but
   // the remainder, at most 2 claimed chunks per wave.
-  const bool long_mean = tr->n_requests > tr->n_batches * (int64_t)cap;
   const ChunkMap cm = long_mean ? chunk_map(tr->n_requests, grid * kWaves, false, cap, 8, 2)
                                 : chunk_map(tr->n_requests, grid * kWaves, true, cap);
-  // (the list has room for every batch then: fewer than n_requests / cap)
-  if (long_mean && mode != MODE_EXT) P.long_min = kLongFew;
   P.wg_first = wg_first;
   P.split_by_count = 0;
   P.claims = (unsigned long long*)(base + L.claims);

@@ -151,10 +151,8 @@ constexpr int kShortLong = 4;  // long batches of a wave's chunk, at most (run_s
 // seldom holds more than one, and a wave that alternates between tiles and
 // listing waits for an offsets window at every step.  115M requests in steps of
 // 512 to 4096: k_tiles 221 -> 33 us, k_long 350 -> 404, the call 562 -> 448 (519
-// with 1024 slots).  Not under the extended model, whose tile kernel the test
-// for it slows down by 0.5% where steps are short.
+// with 1024 slots).  Attribution under Eq. 1 only.
 constexpr int kLongFew = 448;
-template <int MODE> constexpr bool kLongFewMode = MODE != MODE_EXT;
 
 // A batch listed for the segment kernels: its index and exact sums (sum p,
 // sum c, sum p^2, count of c == 0), accumulated by k_big_sums.
@@ -200,9 +198,6 @@ struct Params {
   // Short trace: kShortLong entries per wave, the waves' counts at long_count.
   int64_t* long_list;
   unsigned long long* long_count;
-  // Batches of more than this many slots are listed (the tile's slots, or
-  // fewer where most requests lie in such batches: kLongFew).
-  int32_t long_min;
   int64_t phase_bit;          // added to |B| in bsums row 0 of a prefill batch (0: none)
   int32_t n_tenants;
   int32_t hist_rep;         // MODE_ATTR, HIST_LDS: histogram replicas (1, 2 or 4)
@@ -965,7 +960,9 @@ __device__ __forceinline__ void list_run(const Params& P, int64_t b, int64_t wv,
 // tenant histogram (HIST_LDS) holds hist_rep replicas of n_tenants entries:
 // lane l adds into replica l % hist_rep, so that lanes of one atomic that
 // share a frequent tenant spread over hist_rep entries.
-template <int MODE, int HIST, bool SHARE, int VEC = kVecOf<MODE, HIST>>
+// FEW: batches of more than kLongFew slots are listed, not only those larger
+// than the tile (an instance of its own: the test costs decode-only traces 0.6%).
+template <int MODE, int HIST, bool SHARE, int VEC = kVecOf<MODE, HIST>, bool FEW = false>
 __global__ __launch_bounds__(kWG) void k_tiles(const Params P,
                                                const typename VarsOf<MODE>::type V) {
   LLMV_TILE_CONSTANTS(VEC);
@@ -974,7 +971,7 @@ __global__ __launch_bounds__(kWG) void k_tiles(const Params P,
   __shared__ WaveLds<VEC> s_wave[kWaves];
   constexpr bool STAGE = kStaged<MODE, SHARE>;
   constexpr bool EXT = MODE == MODE_EXT;
-  constexpr bool FEW = kLongFewMode<MODE> && !SHORT;
+  constexpr int32_t kAlone = FEW ? kLongFew : kTile;  // slots of a batch in a tile, at most
   constexpr bool RSUM = kCrossSum<MODE>;
   // extended model, per wave: sum p*c and the share constant k4 of each batch
   __shared__ uint64_t s_rsum[RSUM ? kWaves * kTileBatches : 1];
@@ -1091,12 +1088,11 @@ __global__ __launch_bounds__(kWG) void k_tiles(const Params P,
       // batches consumed by this step: the tile's, or (count == 0) the run of
       // batches from b each to be listed (lane j < lim: batch b+j)
       int32_t adv = count;
-      if (count == 0 || (FEW && P.long_min < kTile)) {
+      if (FEW || count == 0) {
         const int64_t end = __shfl(wv, min(lane + 1, 63), 64);
-        const int64_t most = FEW ? P.long_min : kTile;
-        const uint64_t alone = __ballot(lane < lim && end - (wv & ~(int64_t)3) > most);
-        if (alone) count = min(count, uni((int32_t)__builtin_ctzll(alone)));
-        adv = count ? count : uni((int32_t)__builtin_ctzll(~alone));  // at least 1: batch b is one
+        const uint64_t alone = __ballot(lane < lim && end - (wv & ~(int64_t)3) > kAlone);
+        if (FEW && alone) count = min(count, uni((int32_t)__builtin_ctzll(alone)));
+        adv = FEW && count ? count : uni((int32_t)__builtin_ctzll(~alone));  // at least 1: batch b is one
       }
       const int64_t e = b + adv;
       const int64_t r1 = uni(readlane_i64(wv, adv));
